@@ -108,187 +108,262 @@ __device__ __forceinline__ bool pyr_empty(const SceneArgs& S, int j, const float
   return !((w >> (q[0] & 31)) & 1u);
 }
 
-// Advance this lane's march to its next occupied lattice point.  Returns
-// true with (u, ts, ks) set when a sample was found; sets m.done when the
-// ray leaves the domain.
+// Visit this lane's next lattice point.  Returns true with (u, ts, ks) set
+// when it is a sample (its voxel is occupied); sets m.done when the ray leaves
+// the domain.  Call it only while !m.done.
 // PYR: the scene marches an occupancy pyramid (S.pyr_n > 0) instead of one
 // occupancy grid; a template flag so the single-grid march carries none of it.
 // LO: honour m.t_lo in the contracted domain (points before it are visited
 // without a read).
 template <int DOM, bool PYR, bool LO = false>
-__device__ __forceinline__ bool march_next(const SceneArgs& S, MarchState& m, bool naive,
+__device__ __forceinline__ bool march_step(const SceneArgs& S, MarchState& m, bool naive,
                                            int& reads, float u[3], float& ts, int& ks) {
-  while (!m.done) {
-    if (m.k >= kMaxLattice) { m.done = true; break; }
-    float p[3];
-    float tcur;
-    if (DOM == DOM_BOX) {
-      tcur = m.t0 + (float)m.k * S.step;
-      if (!(tcur < m.t1)) { m.done = true; break; }
-      if (tcur > m.t_hi) { m.done = true; m.stopped_at_hi = true; break; }
+  if (m.k >= kMaxLattice) { m.done = true; return false; }
+  float p[3];
+  float tcur;
+  if (DOM == DOM_BOX) {
+    tcur = m.t0 + (float)m.k * S.step;
+    if (!(tcur < m.t1)) { m.done = true; return false; }
+    if (tcur > m.t_hi) { m.done = true; m.stopped_at_hi = true; return false; }
 #pragma unroll
-      for (int a = 0; a < 3; ++a) p[a] = m.o[a] + tcur * m.d[a];
+    for (int a = 0; a < 3; ++a) p[a] = m.o[a] + tcur * m.d[a];
+  } else {
+    tcur = m.t;
+    if (tcur > m.t_hi) { m.done = true; m.stopped_at_hi = true; return false; }
+    float x[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) x[a] = m.o[a] + tcur * m.d[a];
+    float r2 = (x[0] * x[0] + x[1] * x[1]) + x[2] * x[2];
+    if (!isfinite(r2)) { m.done = true; return false; }
+    if (r2 > 1.0f) {
+      float r = sqrtf(r2);
+      float inv_r = 1.0f / r;
+      float s = (2.0f - inv_r) * inv_r;
+      float xd = ((x[0] * m.d[0] + x[1] * m.d[1]) + x[2] * m.d[2]) * inv_r;
+      if (inv_r < S.step && xd >= 0.0f) { m.done = true; return false; }
+      float perp2 = fmaxf(m.dn2 - xd * xd, 0.0f);
+      float rad = xd * (inv_r * inv_r);
+      const float jn = sqrtf((s * s) * perp2 + rad * rad);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) p[a] = s * x[a];
+      m.t = tcur + S.step / jn;
     } else {
-      tcur = m.t;
-      if (tcur > m.t_hi) { m.done = true; m.stopped_at_hi = true; break; }
-      float x[3];
+      // inside the unit ball |J d| = |d|: the same quotient, taken once per ray
 #pragma unroll
-      for (int a = 0; a < 3; ++a) x[a] = m.o[a] + tcur * m.d[a];
-      float r2 = (x[0] * x[0] + x[1] * x[1]) + x[2] * x[2];
-      if (!isfinite(r2)) { m.done = true; break; }
-      if (r2 > 1.0f) {
-        float r = sqrtf(r2);
-        float inv_r = 1.0f / r;
-        float s = (2.0f - inv_r) * inv_r;
-        float xd = ((x[0] * m.d[0] + x[1] * m.d[1]) + x[2] * m.d[2]) * inv_r;
-        if (inv_r < S.step && xd >= 0.0f) { m.done = true; break; }
-        float perp2 = fmaxf(m.dn2 - xd * xd, 0.0f);
-        float rad = xd * (inv_r * inv_r);
-        const float jn = sqrtf((s * s) * perp2 + rad * rad);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) p[a] = s * x[a];
-        m.t = tcur + S.step / jn;
-      } else {
-        // inside the unit ball |J d| = |d|: the same quotient, taken once per ray
-#pragma unroll
-        for (int a = 0; a < 3; ++a) p[a] = x[a];
-        m.t = tcur + m.dt_in;
-      }
+      for (int a = 0; a < 3; ++a) p[a] = x[a];
+      m.t = tcur + m.dt_in;
     }
-    const int kcur = m.k;
-    bool need = true;
-    if (!naive && DOM == DOM_CONTRACT && m.has_ball) {
-      float e0 = p[0] - m.bc[0], e1 = p[1] - m.bc[1], e2 = p[2] - m.bc[2];
-      float dd = (e0 * e0 + e1 * e1) + e2 * e2;
-      need = !(dd < m.br2);
-    }
-    m.k = kcur + 1;
-    if (!need) continue;
-    if (LO && DOM == DOM_CONTRACT && tcur < m.t_lo) continue;
-    const uint32_t v = voxel_of(S, p, u);
-    if (PYR) {
-      // multi-level occupancy (Eq. 9's s_O branch): levels coarse to fine;
-      // reads counts marching points (lattice points checked), whatever the
-      // number of levels read there
-      ++reads;
-      // the coarsest empty level decides.  The distance grid's word carries
-      // it for the levels at and above the grid's resolution (one read for
-      // the code and G); only when all of those are occupied are the finer
-      // levels read, coarse to fine.  The exhaustive march reads level 0.
-      int lev = -1;
-      uint32_t word = 0;
-      if (naive) {
-        lev = pyr_empty(S, 0, u) ? 0 : -1;
-      } else if (S.pwide) {
-        // the finest level is the one below the distance grid: the word also
-        // holds the voxel's 8 children there (level-0 cell = the voxel's
-        // coordinates doubled plus the child offsets, exactly, since u * 2R
-        // and u * R differ by a power of two)
-        word = S.pwide[v];
-        const uint32_t code = (word >> 9) & 7u;
-        if (code) {
-          lev = int(code);
-        } else {
-          int q0[3];
-          pyr_cell(u, S.pyrR[0], q0);
-          const uint32_t c = uint32_t(q0[0] & 1) | (uint32_t(q0[1] & 1) << 1) | (uint32_t(q0[2] & 1) << 2);
-          lev = ((word >> (16 + c)) & 1u) ? -1 : 0;
-        }
-      } else {
-        word = S.grid[v];
-        const uint32_t code = (word >> 9) & 7u;
-        if (code) {
-          lev = S.pyr_jg + int(code) - 1;
-        } else {
-          for (int j = S.pyr_jg - 1; j >= 0; --j)
-            if (pyr_empty(S, j, u)) {
-              lev = j;
-              break;
-            }
-        }
-      }
-      if (lev < 0) {
-        ts = tcur;
-        ks = kcur;
-        if (!naive && DOM == DOM_CONTRACT) m.has_ball = false;
-        return true;
-      }
-      if (naive) continue;
-      int Rl = S.pyrR[0];
-#pragma unroll
-      for (int j = 1; j < kMaxPyr; ++j) Rl = lev == j ? S.pyrR[j] : Rl;
-      int qe[3];
-      pyr_cell(u, Rl, qe);
-      const bool use_g = S.use_dist && Rl < S.R;
-      const uint32_t g = use_g ? (word & 0xFFu) : 0u;
-      const float vj = (-S.lo - S.lo) / (float)Rl;
-      if (DOM == DOM_BOX) {
-        float te = __int_as_float(0x7F800000);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          if (m.d[a] != 0.0f) {
-            const float b = S.lo + (float)(qe[a] + (m.d[a] > 0.0f ? 1 : 0)) * vj;
-            te = fminf(te, (b - m.o[a]) / m.d[a]);
-          }
-        }
-        const float jo = floorf((te - tcur) / S.step);
-        int jump = jo >= 1.0f ? (jo < (float)kMaxLattice ? (int)jo : kMaxLattice) : 1;
-        if (use_g && g > 0) {
-          const float jf = floorf((float)g * m.rho);
-          const int jg = jf < (float)kMaxLattice ? (int)jf : kMaxLattice;
-          jump = jg > jump ? jg : jump;
-        }
-        m.k = kcur + jump;
-      } else {
-        float r = __int_as_float(0x7F800000);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          const float lower = S.lo + (float)qe[a] * vj;
-          const float upper = S.lo + (float)(qe[a] + 1) * vj;
-          r = fminf(r, fminf(p[a] - lower, upper - p[a]));
-        }
-        const float margin = S.vox * 0.0009765625f;
-        const float ro = r - margin;
-        const float rg = (use_g && g > 0) ? (float)g * S.vox - margin : -__int_as_float(0x7F800000);
-        const float rb = fmaxf(ro, rg);
-        if (rb > 0.0f) {
-          m.br2 = rb * rb;
-          m.bc[0] = p[0]; m.bc[1] = p[1]; m.bc[2] = p[2];
-          m.has_ball = true;
-        } else {
-          m.has_ball = false;
-        }
-      }
-      continue;
-    }
-    const uint32_t word = S.grid[v];
+  }
+  const int kcur = m.k;
+  bool need = true;
+  if (!naive && DOM == DOM_CONTRACT && m.has_ball) {
+    float e0 = p[0] - m.bc[0], e1 = p[1] - m.bc[1], e2 = p[2] - m.bc[2];
+    float dd = (e0 * e0 + e1 * e1) + e2 * e2;
+    need = !(dd < m.br2);
+  }
+  m.k = kcur + 1;
+  if (!need) return false;
+  if (LO && DOM == DOM_CONTRACT && tcur < m.t_lo) return false;
+  const uint32_t v = voxel_of(S, p, u);
+  if (PYR) {
+    // multi-level occupancy (Eq. 9's s_O branch): levels coarse to fine;
+    // reads counts marching points (lattice points checked), whatever the
+    // number of levels read there
     ++reads;
-    if (word & 0x100u) {
+    // the coarsest empty level decides.  The distance grid's word carries
+    // it for the levels at and above the grid's resolution (one read for
+    // the code and G); only when all of those are occupied are the finer
+    // levels read, coarse to fine.  The exhaustive march reads level 0.
+    int lev = -1;
+    uint32_t word = 0;
+    if (naive) {
+      lev = pyr_empty(S, 0, u) ? 0 : -1;
+    } else if (S.pwide) {
+      // the finest level is the one below the distance grid: the word also
+      // holds the voxel's 8 children there (level-0 cell = the voxel's
+      // coordinates doubled plus the child offsets, exactly, since u * 2R
+      // and u * R differ by a power of two)
+      word = S.pwide[v];
+      const uint32_t code = (word >> 9) & 7u;
+      if (code) {
+        lev = int(code);
+      } else {
+        int q0[3];
+        pyr_cell(u, S.pyrR[0], q0);
+        const uint32_t c = uint32_t(q0[0] & 1) | (uint32_t(q0[1] & 1) << 1) | (uint32_t(q0[2] & 1) << 2);
+        lev = ((word >> (16 + c)) & 1u) ? -1 : 0;
+      }
+    } else {
+      word = S.grid[v];
+      const uint32_t code = (word >> 9) & 7u;
+      if (code) {
+        lev = S.pyr_jg + int(code) - 1;
+      } else {
+        for (int j = S.pyr_jg - 1; j >= 0; --j)
+          if (pyr_empty(S, j, u)) {
+            lev = j;
+            break;
+          }
+      }
+    }
+    if (lev < 0) {
       ts = tcur;
       ks = kcur;
       if (!naive && DOM == DOM_CONTRACT) m.has_ball = false;
       return true;
     }
-    const uint32_t g = word & 0xFFu;
-    if (!naive) {
-      if (DOM == DOM_BOX) {
-        if (g > 0) {
-          const float jf = floorf((float)g * m.rho);
-          const int jump = jf < (float)kMaxLattice ? (int)jf : kMaxLattice;
-          m.k = kcur + (jump > 1 ? jump : 1);
+    if (naive) return false;
+    int Rl = S.pyrR[0];
+#pragma unroll
+    for (int j = 1; j < kMaxPyr; ++j) Rl = lev == j ? S.pyrR[j] : Rl;
+    int qe[3];
+    pyr_cell(u, Rl, qe);
+    const bool use_g = S.use_dist && Rl < S.R;
+    const uint32_t g = use_g ? (word & 0xFFu) : 0u;
+    const float vj = (-S.lo - S.lo) / (float)Rl;
+    if (DOM == DOM_BOX) {
+      float te = __int_as_float(0x7F800000);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        if (m.d[a] != 0.0f) {
+          const float b = S.lo + (float)(qe[a] + (m.d[a] > 0.0f ? 1 : 0)) * vj;
+          te = fminf(te, (b - m.o[a]) / m.d[a]);
         }
+      }
+      const float jo = floorf((te - tcur) / S.step);
+      int jump = jo >= 1.0f ? (jo < (float)kMaxLattice ? (int)jo : kMaxLattice) : 1;
+      if (use_g && g > 0) {
+        const float jf = floorf((float)g * m.rho);
+        const int jg = jf < (float)kMaxLattice ? (int)jf : kMaxLattice;
+        jump = jg > jump ? jg : jump;
+      }
+      m.k = kcur + jump;
+    } else {
+      float r = __int_as_float(0x7F800000);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const float lower = S.lo + (float)qe[a] * vj;
+        const float upper = S.lo + (float)(qe[a] + 1) * vj;
+        r = fminf(r, fminf(p[a] - lower, upper - p[a]));
+      }
+      const float margin = S.vox * 0.0009765625f;
+      const float ro = r - margin;
+      const float rg = (use_g && g > 0) ? (float)g * S.vox - margin : -__int_as_float(0x7F800000);
+      const float rb = fmaxf(ro, rg);
+      if (rb > 0.0f) {
+        m.br2 = rb * rb;
+        m.bc[0] = p[0]; m.bc[1] = p[1]; m.bc[2] = p[2];
+        m.has_ball = true;
       } else {
-        if (g > 0) {
-          float rb = (float)g * S.vox - S.vox * 0.0009765625f;
-          m.br2 = rb * rb;
-          m.bc[0] = p[0]; m.bc[1] = p[1]; m.bc[2] = p[2];
-          m.has_ball = true;
-        } else {
-          m.has_ball = false;
-        }
+        m.has_ball = false;
+      }
+    }
+    return false;
+  }
+  const uint32_t word = S.grid[v];
+  ++reads;
+  if (word & 0x100u) {
+    ts = tcur;
+    ks = kcur;
+    if (!naive && DOM == DOM_CONTRACT) m.has_ball = false;
+    return true;
+  }
+  const uint32_t g = word & 0xFFu;
+  if (!naive) {
+    if (DOM == DOM_BOX) {
+      if (g > 0) {
+        const float jf = floorf((float)g * m.rho);
+        const int jump = jf < (float)kMaxLattice ? (int)jf : kMaxLattice;
+        m.k = kcur + (jump > 1 ? jump : 1);
+      }
+    } else {
+      if (g > 0) {
+        float rb = (float)g * S.vox - S.vox * 0.0009765625f;
+        m.br2 = rb * rb;
+        m.bc[0] = p[0]; m.bc[1] = p[1]; m.bc[2] = p[2];
+        m.has_ball = true;
+      } else {
+        m.has_ball = false;
       }
     }
   }
+  return false;
+}
+
+// The grid coordinate of the lattice point at t: the values march_step took
+// there, by the same operations.
+template <int DOM>
+__device__ __forceinline__ void lattice_coord(const SceneArgs& S, const MarchState& m, float t, float u[3]) {
+  float x[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) x[a] = m.o[a] + t * m.d[a];
+  if (DOM == DOM_CONTRACT) {
+    const float r2 = (x[0] * x[0] + x[1] * x[1]) + x[2] * x[2];
+    if (r2 > 1.0f) {
+      const float inv_r = 1.0f / sqrtf(r2);
+      const float s = (2.0f - inv_r) * inv_r;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) x[a] = s * x[a];
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) u[a] = (x[a] - S.lo) * S.inv_ext;
+}
+
+// Samples a wave's march has found ahead of their evaluation: a ring of
+// kAhead entries per lane in this wave's LDS slab (entry e of lane i at
+// e * 64 + i, so a wave's accesses are consecutive words; a lane touches its
+// own entries only, so no barrier is needed).
+//
+// Why: the lanes of a wave reach their next sample after different numbers of
+// lattice points, and a wave that marched every lane to its next sample before
+// each evaluation paid the longest gap of the 64 rays at each of its ~16
+// evaluations: on a 1920x1080 view of the contracted scene 249 march steps
+// a wave on average where its longest ray takes 165, and 7,800 on the wave
+// with the most silhouettes, which alone then held the launch for 6 ms.  Here
+// the wave marches only while some lane has no sample at hand, and the others
+// use those steps to run ahead, so gaps at different samples overlap.  A lane
+// that has run ahead of its ray's termination has only spent steps the wave
+// took anyway; its entries are dropped and its read count is the last
+// evaluated sample's.
+constexpr int kAhead = 8;
+
+struct SampleRing {
+  float* t;             // this wave's slab: kAhead * 64 lattice t
+  int32_t* reads;       // grid reads of the ray up to and including the entry's
+  int32_t* k;           // lattice index (NULL: not kept)
+  int head, count;
+};
+
+constexpr int kRingWords = kAhead * 64;
+
+// March until every lane that can still find a sample has one in its ring
+// (or no ray of the wave goes on).  All 64 lanes must call it together.
+template <int DOM, bool PYR, bool LO, bool KEEP_K>
+__device__ __forceinline__ void march_ahead(const SceneArgs& S, MarchState& m, bool naive, int& reads,
+                                            SampleRing& q, int lane) {
+  while (__ballot(!m.done && q.count == 0) != 0) {
+    if (!m.done && q.count < kAhead) {
+      float u[3], ts;
+      int ks;
+      if (march_step<DOM, PYR, LO>(S, m, naive, reads, u, ts, ks)) {
+        const int at = ((q.head + q.count) & (kAhead - 1)) * 64 + lane;
+        q.t[at] = ts;
+        q.reads[at] = reads;
+        if (KEEP_K) q.k[at] = ks;
+        ++q.count;
+      }
+    }
+  }
+}
+
+// Advance this lane's march to its next occupied lattice point.  Returns
+// true with (u, ts, ks) set when a sample was found.
+template <int DOM, bool PYR, bool LO = false>
+__device__ __forceinline__ bool march_next(const SceneArgs& S, MarchState& m, bool naive,
+                                           int& reads, float u[3], float& ts, int& ks) {
+  while (!m.done)
+    if (march_step<DOM, PYR, LO>(S, m, naive, reads, u, ts, ks)) return true;
   return false;
 }
 

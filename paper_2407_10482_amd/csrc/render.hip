@@ -4,11 +4,12 @@
 // One lane owns one ray; a wave owns 64 rays (an 8x8 pixel tile when the
 // caller orders rays tile-major, which keeps the coarse-level gathers of a
 // wave on shared cache lines; neighbouring rays also march alike, so the
-// wave's lanes finish within a sample or two of each other).  Each iteration every live lane first marches
-// to its next occupied lattice point (divergent but cheap: one 2-byte grid
-// read per marching point, none inside a known-empty region), then all lanes
-// holding a sample evaluate it together (the gather-heavy part runs with the
-// wave converged).  After the last ray of the wave finishes, the wave runs
+// wave's lanes finish within a sample or two of each other).  Each iteration
+// the wave marches until every live lane has a sample at hand (one 2-byte
+// grid read per marching point, none inside a known-empty region; lanes that
+// have one run ahead meanwhile, SampleRing), then all lanes take the first of
+// theirs and evaluate it together (the gather-heavy part runs with the wave
+// converged).  After the last ray of the wave finishes, the wave runs
 // the deferred MLP for its 64 rays with v_mfma_f32_16x16x4_f32.
 #include <hip/hip_runtime.h>
 
@@ -134,7 +135,12 @@ render_kernel(SceneArgs S, int64_t n, const float* __restrict__ O,
                                                      const float* __restrict__ D, RayOut out,
                                                      MarchRecord rec, const float* __restrict__ mlp,
                                                      int naive, ProposalArgs pa) {
+  constexpr bool EXT = MODE == MODE_RENDER_EXT;
+  constexpr bool KEEP_K = EXT || MODE == MODE_MARCH;    // the samples' lattice indices are used
   __shared__ float xin_all[4][8 * 64];
+  __shared__ float ring_t[4][kRingWords];
+  __shared__ int32_t ring_reads[4][kRingWords];
+  __shared__ int32_t ring_k[KEEP_K ? 4 : 1][KEEP_K ? kRingWords : 1];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
 #if NGPRT_XCD_CHUNK > 0
@@ -158,7 +164,6 @@ render_kernel(SceneArgs S, int64_t n, const float* __restrict__ O,
   const float* oray = O + 3 * (in_range ? ray : 0);
   const float* dray = D + 3 * (in_range ? ray : 0);
   march_init<DOM>(S, oray, dray, in_range, m);
-  constexpr bool EXT = MODE == MODE_RENDER_EXT;
   bool proposed = false, fell_back = false;
   if (EXT && (pa.prop || pa.net_w)) {
     float q[4];
@@ -200,28 +205,47 @@ render_kernel(SceneArgs S, int64_t n, const float* __restrict__ O,
   bool half_set = false, far_set = false;
   // distortion regulariser: running sums of w, w m and w (m W_< - S_<), and w^2
   float dW = 0.0f, dS = 0.0f, dP = 0.0f, dQ = 0.0f;
-  int ns = 0, reads = 0;
+  int ns = 0, reads = 0;        // reads: of the march, which may be ahead of the samples
+  int reads_at = 0;             // up to the last evaluated sample
+  bool ended = false;           // by transmittance or the sample cap
+  constexpr bool PYR = (MODEL & 2) != 0;
+  SampleRing ring{ring_t[wave], ring_reads[wave], KEEP_K ? ring_k[KEEP_K ? wave : 0] : nullptr, 0, 0};
 
   for (;;) {
-    float u[3], ts;
-    int ks;
-    bool have = march_next<DOM, (MODEL & 2) != 0, EXT>(S, m, naive != 0, reads, u, ts, ks);
-    if (EXT && !have && proposed && !fell_back) {
-      if (ns == 0) {
-        // the proposed interval holds no occupied lattice point: march again
-        // from the start as the plain march
-        march_init<DOM>(S, oray, dray, in_range, m);
-        fell_back = true;
-        have = march_next<DOM, (MODEL & 2) != 0, EXT>(S, m, naive != 0, reads, u, ts, ks);
-      } else if (m.stopped_at_hi && pa.far_guard > 0.0f && !(T < pa.far_guard)) {
-        // at the proposed far end with too much transmittance left: march on
-        m.t_hi = __int_as_float(0x7F800000);
-        m.done = false;
-        m.stopped_at_hi = false;
-        have = march_next<DOM, (MODEL & 2) != 0, EXT>(S, m, naive != 0, reads, u, ts, ks);
+    march_ahead<DOM, PYR, EXT, KEEP_K>(S, m, naive != 0, reads, ring, lane);
+    if constexpr (EXT) {
+      // a proposed ray at the end of its interval with every sample evaluated
+      bool resumed = false;
+      if (ring.count == 0 && proposed && !fell_back && !ended) {
+        if (ns == 0) {
+          // the proposed interval holds no occupied lattice point: march again
+          // from the start as the plain march
+          march_init<DOM>(S, oray, dray, in_range, m);
+          fell_back = true;
+          resumed = true;
+        } else if (m.stopped_at_hi && pa.far_guard > 0.0f && !(T < pa.far_guard)) {
+          // at the proposed far end with too much transmittance left: march on
+          m.t_hi = __int_as_float(0x7F800000);
+          m.done = false;
+          m.stopped_at_hi = false;
+          resumed = true;
+        }
       }
+      if (__ballot(resumed) != 0) march_ahead<DOM, PYR, EXT, KEEP_K>(S, m, naive != 0, reads, ring, lane);
     }
+    const bool have = ring.count > 0;
     if (__ballot(have) == 0) break;
+    float u[3] = {0.f, 0.f, 0.f}, ts = 0.0f;
+    int ks = 0;
+    if (have) {
+      const int at = ring.head * 64 + lane;
+      ts = ring.t[at];
+      reads_at = ring.reads[at];
+      if (KEEP_K) ks = ring.k[at];
+      ring.head = (ring.head + 1) & (kAhead - 1);
+      --ring.count;
+      lattice_coord<DOM>(S, m, ts, u);
+    }
     if (have) {
       float f[8];
       eval_sample<MODEL & 5, DT, LMAX>(S, u, f);
@@ -248,9 +272,14 @@ render_kernel(SceneArgs S, int64_t n, const float* __restrict__ O,
         if (!far_set && T < 1e-3f) { t_far = ts; far_set = true; }
       }
       ++ns;
-      if (T < S.thr || ns >= S.max_samples) m.done = true;
+      if (T < S.thr || ns >= S.max_samples) {
+        m.done = true;
+        ended = true;
+        ring.count = 0;
+      }
     }
   }
+  if (ended) reads = reads_at;
   if (!half_set) t_half = t_last;
   if (!far_set) t_far = t_last;
 
