@@ -17,18 +17,11 @@
 //          P_i the running sum of w_j s_j; then the softmax adjoint
 //          dL/da_l = w_l (dL/df . v_l - dL/df . f) and the trilinear scatter of
 //          every level's 9-channel gradient into its 8 corner entries with
-//          hardware float atomics (order-nondeterministic sums).  The wave
-//          first sums the contributions to equal entries (neighbouring rays'
-//          samples share cells) so one lane issues each entry's atomics:
-//          per corner slot the 64 (entry, lane) words are sorted across the
-//          wave (a bitonic network on DPP and swizzle lane moves), runs of
-//          equal entries are summed by a segmented scan, and the last lane
-//          of each run issues the atomics.  Measured on 2^18-ray training
-//          batches (backward kernel): 16 x 2^19 tables 174 -> 92 ms, 8 x 2^14
-//          35 -> 14 ms against one pass per distinct entry with a butterfly
-//          sum each; spreading each run's 9 channel atomics over neighbouring
-//          lanes of one instruction (scatter_runs) then 92 -> 20 ms and
-//          14 -> 7 ms.
+//          hardware float atomics (order-nondeterministic sums).  The dot
+//          products dL/df . v_l come from two sums a level that the sample's
+//          one lookup leaves behind (GradSink), not from a second gather.
+//          The wave first merges the samples of equal cells, whose eight
+//          corner rows then leave as one row each (scatter_cells).
 //          The baked model scatters into its fine levels and coarse atlas
 //          rows instead (baked_scatter).  In the deterministic mode each
 //          contribution goes to a record of its own instead (det.hip).
@@ -47,13 +40,6 @@ namespace ngprt {
 typedef float bf32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kPad = 17;   // LDS row pitch of the per-wave staging (bank spread)
-
-// Levels of at least this resolution merge equal table entries across the
-// wave by sorting (wave_sort_merge); coarser levels, where a wave's samples
-// share a handful of cells, by the leader loop (one pass per distinct entry).
-#ifndef NGPRT_BW_SORT_MIN_RES
-#define NGPRT_BW_SORT_MIN_RES 16
-#endif
 
 // value of lane (lane ^ J) for every lane of a full wave; J = 1, 2, 4, 8 by
 // DPP lane moves (quad_perm, row_half_mirror, row_mirror), 16 by ds_swizzle,
@@ -75,45 +61,6 @@ __device__ __forceinline__ uint32_t lane_xor(uint32_t v, int lane) {
   return uint32_t(__builtin_amdgcn_ds_bpermute((lane ^ 32) << 2, x));
 }
 
-constexpr int kStageRow = 17;   // staged run: up to 16 values and the key
-
-// The atomics of a merged level.  The 9 (NV) channels of each run's row go to
-// neighbouring lanes of one atomic instruction, so an instruction carries the
-// rows of about 7 runs, 9 consecutive floats each: the tail lanes (one per
-// run) stage key and values in this wave's LDS slab `stage` (64 x 17 words),
-// then lane q of each pass adds value q % NV of run q / NV.  Measured on
-// 2^18-ray training batches (backward kernel, 16 x 2^19 / 8 x 2^14 tables):
-// 91.6 / 14.5 ms with 9 one-lane-per-run instructions, 19.8 / 7.0 ms spread
-// (the same-line atomics of one instruction are combined on their way to
-// memory).
-// Rows are `stride` floats apart (9 for the tables, C for the coarse atlas);
-// only the first nv <= NV channels are added.
-template <int NV>
-__device__ __forceinline__ void scatter_runs(float* __restrict__ gbase, bool tail, uint32_t key, const float x[NV],
-                                             int lane, float* stage, int stride = 9, int nv = NV) {
-  static_assert(NV < kStageRow, "a staged row holds the values and the key");
-  const uint64_t tm = __ballot(tail);
-  const int m = __popcll(tm);
-  if (tail) {
-    const int rank = __builtin_amdgcn_mbcnt_hi(uint32_t(tm >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(tm), 0));
-    float* row = stage + rank * kStageRow;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) row[j] = x[j];
-    row[kStageRow - 1] = __uint_as_float(key);
-  }
-  // the other lanes' staged rows are read below: a wave-scope fence orders
-  // the LDS stores before the loads (and the next call's stores after them)
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  for (int q = lane; q < nv * m; q += 64) {
-    const int t = q / nv, c = q - t * nv;
-    const float* row = stage + t * kStageRow;
-    unsafeAtomicAdd(gbase + size_t(__float_as_uint(row[kStageRow - 1])) * size_t(stride) + c, row[c]);
-  }
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-}
-
 // one compare-exchange stage of a bitonic sort over the wave's 64 lanes
 template <int K, int J>
 __device__ __forceinline__ uint32_t bitonic_stage(uint32_t v, int lane) {
@@ -123,16 +70,8 @@ __device__ __forceinline__ uint32_t bitonic_stage(uint32_t v, int lane) {
   return keep_min ? lo : hi;
 }
 
-// Sums the NV values of the wave's lanes that hold the same key (an entry
-// index below 2^26; lanes with active = false take no part).  Sorting the
-// words (key << 6 | lane) puts equal keys on neighbouring lanes; each lane
-// fetches the values of the lane whose word it holds, runs of equal keys are
-// summed by a scan (skipped when no key repeats) and the last lane of each
-// run returns true with the run's key and sum in key, v.  Every lane of the
-// wave must call this with all 64 lanes active.
-template <int NV>
-__device__ __forceinline__ bool wave_sort_merge(uint32_t& key, bool active, float v[NV], int lane) {
-  uint32_t w = active ? ((key << 6) | uint32_t(lane)) : 0xFFFFFFFFu;
+// Ascending sort of one word per lane over the wave's 64 lanes.
+__device__ __forceinline__ uint32_t wave_sort(uint32_t w, int lane) {
   w = bitonic_stage<2, 1>(w, lane);
   w = bitonic_stage<4, 2>(w, lane);   w = bitonic_stage<4, 1>(w, lane);
   w = bitonic_stage<8, 4>(w, lane);   w = bitonic_stage<8, 2>(w, lane);   w = bitonic_stage<8, 1>(w, lane);
@@ -142,35 +81,173 @@ __device__ __forceinline__ bool wave_sort_merge(uint32_t& key, bool active, floa
   w = bitonic_stage<32, 2>(w, lane);  w = bitonic_stage<32, 1>(w, lane);
   w = bitonic_stage<64, 32>(w, lane); w = bitonic_stage<64, 16>(w, lane); w = bitonic_stage<64, 8>(w, lane);
   w = bitonic_stage<64, 4>(w, lane);  w = bitonic_stage<64, 2>(w, lane);  w = bitonic_stage<64, 1>(w, lane);
-  const bool valid = w != 0xFFFFFFFFu;
-  const int src = int(w & 63u);
-  const uint32_t k = w >> 6;
-  float x[NV];
+  return w;
+}
+
+// LDS of one wave for scatter_cells, in floats: the samples' corner weights
+// [64][8], row indices [64][8] and gradients [64][16] (the last sized for the
+// widest row), in sorted order.  Shared with the MLP's staging (2 x 64 x kPad),
+// which is done before the first scatter.
+constexpr int kStageW = 0, kStageI = 64 * 8, kStageG = 2 * 64 * 8, kStageFloats = 2 * 64 * kPad;
+static_assert(kStageG + 64 * 16 <= kStageFloats, "staging slab");
+
+constexpr uint32_t kNoRow = 0xFFFFFFFFu;
+
+// Adds w[k] * g[j] to gbase[idx[k] * stride + j] (k < 8 corners, j < nv <= NV
+// channels; idx kNoRow: no such row) for every lane with have set, summing the
+// lanes of equal cells (key0, key1) first.  Every lane of the wave calls it.
+//
+// What bounds it: the memory side takes float atomics as requests of 64 bytes
+// at 21 G a second whatever their address, order, scope or working set (a
+// probe over 0.15 to 302 MB), so the rows that leave the wave are what a
+// scatter costs; next to that, the instructions of merging them.  A cell's
+// samples share all eight corner rows, so the wave sorts its 64 samples by
+// cell once a level (not once a corner), and the sum over a cell's samples of
+// the outer product w (8) x g (9) is a matrix product with the samples as K:
+// v_mfma_f32_16x16x4_f32 takes two cells at a time (rows: their 2 x 8 corners;
+// columns: up to 16 channels; the sorted samples of a cell are contiguous, so
+// two cells take one or two instructions when nothing repeats and 16 when the
+// wave shares one).  Its result rows go from the accumulators straight to the
+// atomics, each row's channels on neighbouring lanes so that a row is one or
+// two requests; x-adjacent corners (neighbouring rows for even x) share an
+// instruction, which the memory side merges when they share a line.
+// Measured (training step of 2^18 rays, tables 8 x 2^14 / 16 x 2^19): a sort and
+// scan a corner, with a second gather of the level's rows, 7.49 / 21.7 ms; this
+// 3.70 / 17.9 ms (before lanes a ray and padded rows, below).
+// A wave that holds a non-finite gradient adds its contributions lane by lane
+// instead: in a matrix product it would reach the other cell's rows too.
+template <int NV>
+__device__ __forceinline__ void scatter_cells(float* __restrict__ gbase, int stride, int nv, bool have,
+                                              uint32_t key0, uint32_t key1, const uint32_t idx[8],
+                                              const float w[8], const float g[NV], int lane, float* stage) {
+  const uint64_t active = __ballot(have);
+  if (active == 0) return;
+  const int na = __popcll(active);
+  float mag = 0.0f;
 #pragma unroll
-  for (int j = 0; j < NV; ++j)
-    x[j] = __int_as_float(__builtin_amdgcn_ds_bpermute(src << 2, __float_as_int(v[j])));
-  // neighbours' keys (sentinels sort last, so a valid lane's successor is
-  // either valid or the sentinel)
-  const uint32_t next = uint32_t(__builtin_amdgcn_ds_bpermute(((lane + 1) & 63) << 2, int(k)));
-  const bool tail = valid && (lane == 63 || next != k);
-  // segmented inclusive scan over runs of equal keys (Hillis-Steele), only
-  // as far as the longest run needs
+  for (int j = 0; j < NV; ++j) mag += fabsf(g[j]);
+  if (__ballot(have && !(mag < __int_as_float(0x7F800000))) != 0) {
+    if (have) {
 #pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t pk = uint32_t(__builtin_amdgcn_ds_bpermute(((lane - d) & 63) << 2, int(k)));
-    const bool same = valid && lane >= d && pk == k;
-    if (__ballot(same) == 0) break;
+      for (int k = 0; k < 8; ++k)
+        if (idx[k] != kNoRow) {
+          float* dst = gbase + size_t(idx[k]) * size_t(stride);
+          for (int j = 0; j < NV; ++j)
+            if (j < nv) unsafeAtomicAdd(dst + j, w[k] * g[j]);
+        }
+    }
+    return;
+  }
+  // sort by a 25-bit hash of the cell; lanes without a sample go last.  Cells
+  // whose hashes collide only split each other's runs: a run is of equal keys.
+  uint32_t h = (key0 * 0x9E3779B1u) ^ (key1 * 0x85EBCA77u);
+  h ^= h >> 15;
+  const uint32_t word = wave_sort(have ? (((h >> 1) & ~63u) | uint32_t(lane)) : (0xFFFFFFC0u | uint32_t(lane)), lane);
+  const int src = int(word & 63u);
+  const uint32_t k0 = uint32_t(__builtin_amdgcn_ds_bpermute(src << 2, int(key0)));
+  const uint32_t k1 = uint32_t(__builtin_amdgcn_ds_bpermute(src << 2, int(key1)));
+  const uint32_t p0 = __shfl_up(k0, 1, 64), p1 = __shfl_up(k1, 1, 64);
+  uint64_t heads = __ballot(lane < na && (lane == 0 || k0 != p0 || k1 != p1));
+  // the sample's place in the sorted order, at its own lane
+  const int row = __builtin_amdgcn_ds_permute(src << 2, lane);
+  float* sW = stage + kStageW;
+  uint32_t* sI = reinterpret_cast<uint32_t*>(stage + kStageI);
+  float* sG = stage + kStageG;
+  constexpr int GP = NV <= 12 ? 12 : 16;
+  if (have) {
+    float4* dw = reinterpret_cast<float4*>(sW + row * 8);
+    dw[0] = make_float4(w[0], w[1], w[2], w[3]);
+    dw[1] = make_float4(w[4], w[5], w[6], w[7]);
+    // corners by the accumulator layout: even ones, then odd ones
+    uint4* di = reinterpret_cast<uint4*>(sI + row * 8);
+    di[0] = make_uint4(idx[0], idx[2], idx[4], idx[6]);
+    di[1] = make_uint4(idx[1], idx[3], idx[5], idx[7]);
+    float4* dg = reinterpret_cast<float4*>(sG + row * GP);
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const float o = __int_as_float(__builtin_amdgcn_ds_bpermute(((lane - d) & 63) << 2, __float_as_int(x[j])));
-      x[j] = same ? x[j] + o : x[j];
+    for (int q = 0; q < GP / 4; ++q) {
+      float4 t;
+      t.x = 4 * q < NV ? g[4 * q < NV ? 4 * q : 0] : 0.0f;
+      t.y = 4 * q + 1 < NV ? g[4 * q + 1 < NV ? 4 * q + 1 : 0] : 0.0f;
+      t.z = 4 * q + 2 < NV ? g[4 * q + 2 < NV ? 4 * q + 2 : 0] : 0.0f;
+      t.w = 4 * q + 3 < NV ? g[4 * q + 3 < NV ? 4 * q + 3 : 0] : 0.0f;
+      dg[q] = t;
     }
   }
-#pragma unroll
-  for (int j = 0; j < NV; ++j) v[j] = x[j];
-  key = k;
-  return tail;
+  // the other lanes' rows are read below: a wave-scope fence orders the LDS
+  // stores before the loads (and the next call's stores after them)
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const int i = lane & 15, s = lane >> 4;
+  const int corner = 2 * (i & 3) + ((i >> 2) & 1);      // of accumulator row i
+  while (heads) {
+    const int a0 = __ffsll((unsigned long long)heads) - 1;
+    heads &= heads - 1;
+    const int b0 = heads ? __ffsll((unsigned long long)heads) - 1 : na;
+    heads &= heads - 1;
+    const int end = heads ? __ffsll((unsigned long long)heads) - 1 : na;
+    const int lo = i < 8 ? a0 : b0, hi = i < 8 ? b0 : end;
+    bf32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int c = a0 >> 2; 4 * c < end; ++c) {
+      const int r = 4 * c + s;
+      const float A = (r >= lo && r < hi) ? sW[r * 8 + corner] : 0.0f;
+      const float B = (r >= a0 && r < end && i < GP) ? sG[r * GP + i] : 0.0f;
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(A, B, acc, 0, 0, 0);
+    }
+    const int head = s < 2 ? a0 : b0;
+    if (head < na && i < nv) {
+      const uint4 id = *reinterpret_cast<const uint4*>(sI + head * 8 + 4 * (s & 1));
+      if (id.x != kNoRow) unsafeAtomicAdd(gbase + size_t(id.x) * size_t(stride) + i, acc[0]);
+      if (id.y != kNoRow) unsafeAtomicAdd(gbase + size_t(id.y) * size_t(stride) + i, acc[1]);
+      if (id.z != kNoRow) unsafeAtomicAdd(gbase + size_t(id.z) * size_t(stride) + i, acc[2]);
+      if (id.w != kNoRow) unsafeAtomicAdd(gbase + size_t(id.w) * size_t(stride) + i, acc[3]);
+    }
+  }
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
+
+// What the backward keeps of a sample's lookup, per level: the interpolated
+// logit, density channel A_l = v_l[0] and colour sum
+// B_l = dL/dC_d . v_l[1..3] + dL/dF . v_l[4..7], so that dL/df . v_l =
+// dL/df_0 A_l + w B_l once the sample's weight w is known (dL/df_j = w times
+// the ray's dL/dC_d or dL/dF).  Vectors, so that the rolled level loops index
+// them by a wave-uniform register offset.
+template <int LMAX>
+struct GradSink {
+  typedef float vec __attribute__((ext_vector_type(LMAX)));
+  vec a, A, B;
+  float run_max, esum;
+  const float* gcd;
+  const float* gfv;
+  __device__ __forceinline__ void level(int l, const float* acc, const Corners&) {
+    a[l] = acc[8];
+    A[l] = acc[0];
+    float b = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) b = __builtin_fmaf(gcd[j], acc[1 + j], b);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) b = __builtin_fmaf(gfv[j], acc[4 + j], b);
+    B[l] = b;
+  }
+  __device__ __forceinline__ void done(float m, float e) { run_max = m; esum = e; }
+  // baked model: the level's gates in a and g
+  vec g;
+  __device__ __forceinline__ void gates(int l, float gw, float gb, const float* acc, const Corners&) {
+    float b = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) b = __builtin_fmaf(gcd[j], acc[1 + j], b);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) b = __builtin_fmaf(gfv[j], acc[4 + j], b);
+#pragma unroll
+    for (int q = 0; q < LMAX; ++q)
+      if (q == l) {
+        a[q] = gw;
+        g[q] = gb;
+        A[q] = acc[0];
+        B[q] = b;
+      }
+  }
+};
 
 // D[i][j] = sum over the wave's 64 rays r of A_r[i] * B_r[j] (i, j < 16).
 // sA, sB: [64][kPad].  Lane l returns D[4*(l/16) + q][l%16], q = 0..3.
@@ -185,20 +262,6 @@ __device__ __forceinline__ bf32x4 wave_outer_sum(const float* sA, const float* s
   return acc;
 }
 
-// Corner k of a cell for a loop counter k that is the same on every lane:
-// picked from registers by selects, where indexing the arrays with k would
-// put them in per-lane scratch memory (a store per level and a load per
-// corner through the vector memory pipeline).
-__device__ __forceinline__ void corner_pick(const Corners& c, int k, uint32_t& idx, float& w) {
-  idx = c.idx[0];
-  w = c.w[0];
-#pragma unroll
-  for (int j = 1; j < 8; ++j) {
-    idx = k == j ? c.idx[j] : idx;
-    w = k == j ? c.w[j] : w;
-  }
-}
-
 // Adjoint of the baked feature construction at one sample (Sec. 4.2 Eq. 7-8):
 // with f_0 = f~_0 + sum_l g(omega_l) s_l and f_j = f~_j + sum_l g(beta_l) v_lj
 // (j >= 1), dL/df (gf) gives
@@ -206,19 +269,46 @@ __device__ __forceinline__ void corner_pick(const Corners& c, int k, uint32_t& i
 //   coarse row:    dL/df~_j = gf_j,
 //                  dL/domega_l = gf_0 s_l g'(omega_l),
 //                  dL/dbeta_l = sum_{j>=1} gf_j v_lj g'(beta_l),
-// each spread trilinearly over its 8 corners; g' = g (1 - g).  Vertices of
-// empty blocks take the default vector and receive no gradient.  Every lane
-// of the wave takes part (have = false: no contribution) so that equal
-// entries are summed across the wave before one lane issues their atomics.
-// gtab: [L][T][9] (channel 8, the hash model's logit, untouched); gatlas:
-// [n_blocks][8][8][8][C], C = 8 + 2 L.
+// each spread trilinearly over its 8 corners; g' = g (1 - g).  The gates, s_l
+// and sum_j gf_j v_lj come from the lookup (q; w: the sample's weight).
+// Vertices of empty blocks take the default vector and receive no gradient.
+// Every lane of the wave takes part (have = false: no contribution).
+// gtab: [L][T][tstride] (channel 8, the hash model's logit, untouched); gatlas:
+// [n_blocks][8][8][8][astride], of which C = 8 + 2 L.
 template <int LMAX>
 __device__ __forceinline__ void baked_scatter(const SceneArgs& S, const float u[3], bool have, const float gf[8],
-                                              float* __restrict__ gtab, float* __restrict__ gatlas,
+                                              float w, const GradSink<LMAX>& q, float* __restrict__ gtab,
+                                              int tstride, float* __restrict__ gatlas, int astride, int lane,
                                               float* stage) {
   static_assert(LMAX <= 4, "the coarse row holds at most 16 channels");
   constexpr int CMAX = 8 + 2 * LMAX;
   const int C = 8 + 2 * S.L;
+  float gco[CMAX];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) gco[j] = have ? gf[j] : 0.0f;
+#pragma unroll
+  for (int j = 8; j < CMAX; ++j) gco[j] = 0.0f;
+  const size_t T_entries = size_t(1) << S.log2T;
+#pragma unroll
+  for (int l = 0; l < LMAX; ++l) {
+    if (l >= S.L) break;
+    Corners c;
+    level_corners(u, S.N[l], S.Nf[l], S.mask, c);
+    float gv[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) gv[j] = 0.0f;
+    if (have) {
+      const float gw = q.a[l], gb = q.g[l];
+      gco[8 + 2 * l] = gf[0] * q.A[l] * (gw * (1.0f - gw));
+      gco[9 + 2 * l] = (w * q.B[l]) * (gb * (1.0f - gb));
+      gv[0] = gf[0] * gw;
+#pragma unroll
+      for (int j = 1; j < 8; ++j) gv[j] = gf[j] * gb;
+    }
+    scatter_cells<8>(gtab + (size_t(l) * T_entries) * size_t(tstride), tstride, 8, have, c.key0, c.key1, c.idx, c.w,
+                     gv, lane, stage);
+  }
+  // coarse rows: one vertex = (atlas row, local offset)
   int i0[3];
   float fr[3], gr[3];
 #pragma unroll
@@ -230,158 +320,25 @@ __device__ __forceinline__ void baked_scatter(const SceneArgs& S, const float u[
     fr[a] = __builtin_fmaf(u[a], S.LCf, -(float)i);
     gr[a] = 1.0f - fr[a];
   }
-  // interpolated attention parameters (coarse channels 8 .. 8 + 2L)
-  float ap[2 * LMAX];
+  uint32_t idx[8];
+  float wk[8];
 #pragma unroll
-  for (int j = 0; j < 2 * LMAX; ++j) ap[j] = 0.0f;
-  if (have) {
-#pragma unroll 1
-    for (int k = 0; k < 8; ++k) {
-      const int bx = k & 1, by = (k >> 1) & 1, bz = (k >> 2) & 1;
-      const int vx = i0[0] + bx, vy = i0[1] + by, vz = i0[2] + bz;
-      const int bid = S.cidx[((vz >> 3) * S.nb + (vy >> 3)) * S.nb + (vx >> 3)];
-      const float wk = ((bx ? fr[0] : gr[0]) * (by ? fr[1] : gr[1])) * (bz ? fr[2] : gr[2]);
-      float v[8];
-      if (bid >= 0) {
-        const float4* row = reinterpret_cast<const float4*>(
-            S.catlas + (size_t(bid) * 512 + size_t(((vz & 7) * 8 + (vy & 7)) * 8 + (vx & 7))) * S.Cpad);
-        const float4 q2 = row[2];
-        const float4 q3 = S.Cpad > 12 ? row[3] : make_float4(0.f, 0.f, 0.f, 0.f);
-        v[0] = q2.x; v[1] = q2.y; v[2] = q2.z; v[3] = q2.w;
-        v[4] = q3.x; v[5] = q3.y; v[6] = q3.z; v[7] = q3.w;
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = S.cdef[8 + j];
-      }
-#pragma unroll
-      for (int j = 0; j < 2 * LMAX; ++j) ap[j] = __builtin_fmaf(wk, v[j], ap[j]);
-    }
-  }
-  float gco[CMAX];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) gco[j] = have ? gf[j] : 0.0f;
-#pragma unroll
-  for (int j = 8; j < CMAX; ++j) gco[j] = 0.0f;
-  const size_t T_entries = size_t(1) << S.log2T;
-  // fine levels: values for the gate gradients, then the 8-channel scatter
-#pragma unroll
-  for (int l = 0; l < LMAX; ++l) {
-    if (l >= S.L) break;
-    Corners c;
-    level_corners(u, S.N[l], S.Nf[l], S.mask, c);
-    float gv[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) gv[j] = 0.0f;
-    if (have) {
-      const void* fb = feat_level<DT_F32>(S.feat, l, S.log2T);
-      float acc[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] = 0.0f;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        float v[8];
-        Store<DT_F32>::feat(fb, c.idx[k], v);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = __builtin_fmaf(c.w[k], v[j], acc[j]);
-      }
-      const float gw = sigmoid32(ap[2 * l]), gb = sigmoid32(ap[2 * l + 1]);
-      float tb = 0.0f;
-#pragma unroll
-      for (int j = 1; j < 8; ++j) tb = __builtin_fmaf(gf[j], acc[j], tb);
-      gco[8 + 2 * l] = gf[0] * acc[0] * (gw * (1.0f - gw));
-      gco[9 + 2 * l] = tb * (gb * (1.0f - gb));
-      gv[0] = gf[0] * gw;
-#pragma unroll
-      for (int j = 1; j < 8; ++j) gv[j] = gf[j] * gb;
-    }
-    float* gbase = gtab + (size_t(l) * T_entries) * 9;
-    const int lane = threadIdx.x & 63;
-    if (S.N[l] >= NGPRT_BW_SORT_MIN_RES) {
-#pragma unroll 1
-      for (int k = 0; k < 8; ++k) {
-        uint32_t key;
-        float wk;
-        corner_pick(c, k, key, wk);
-        float x[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = wk * gv[j];
-        const bool tail = wave_sort_merge<8>(key, have, x, lane);
-        scatter_runs<8>(gbase, tail, key, x, lane, stage);
-      }
-      continue;
-    }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      bool pending = have;
-      uint64_t pm = __ballot(pending);
-      while (pm) {
-        const int leader = __ffsll((unsigned long long)pm) - 1;
-        const uint32_t key = __shfl(c.idx[k], leader, 64);
-        const bool mine = pending && c.idx[k] == key;
-        float x[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = mine ? c.w[k] * gv[j] : 0.0f;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) x[j] += __shfl_xor(x[j], off, 64);
-        }
-        if (lane == leader) {
-          float* dst = gbase + size_t(key) * 9;
-#pragma unroll
-          for (int j = 0; j < 8; ++j) unsafeAtomicAdd(dst + j, x[j]);
-        }
-        pending = pending && !mine;
-        pm = __ballot(pending);
-      }
-    }
-  }
-  // coarse rows: one vertex = (atlas row, local offset)
-  const int lane = threadIdx.x & 63;
-#pragma unroll 1
   for (int k = 0; k < 8; ++k) {
     const int bx = k & 1, by = (k >> 1) & 1, bz = (k >> 2) & 1;
     const int vx = i0[0] + bx, vy = i0[1] + by, vz = i0[2] + bz;
     const int bid = have ? S.cidx[((vz >> 3) * S.nb + (vy >> 3)) * S.nb + (vx >> 3)] : -1;
-    const int loc = ((vz & 7) * 8 + (vy & 7)) * 8 + (vx & 7);
-    const float wk = ((bx ? fr[0] : gr[0]) * (by ? fr[1] : gr[1])) * (bz ? fr[2] : gr[2]);
-    if (S.n_blocks <= (1 << 17)) {
-      // vertex key bid * 512 + loc < 2^26: sorted merge and spread atomics
-      uint32_t key = bid >= 0 ? uint32_t(bid) * 512u + uint32_t(loc) : 0u;
-      float x[CMAX];
-#pragma unroll
-      for (int j = 0; j < CMAX; ++j) x[j] = wk * gco[j];
-      const bool tail = wave_sort_merge<CMAX>(key, bid >= 0, x, lane);
-      scatter_runs<CMAX>(gatlas, tail, key, x, lane, stage, C, C);
-      continue;
-    }
-    bool pending = bid >= 0;
-    uint64_t pm = __ballot(pending);
-    while (pm) {
-      const int leader = __ffsll((unsigned long long)pm) - 1;
-      const int kb = __shfl(bid, leader, 64), kl = __shfl(loc, leader, 64);
-      const bool mine = pending && bid == kb && loc == kl;
-      float x[CMAX];
-#pragma unroll
-      for (int j = 0; j < CMAX; ++j) x[j] = mine ? wk * gco[j] : 0.0f;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-        for (int j = 0; j < CMAX; ++j) x[j] += __shfl_xor(x[j], off, 64);
-      }
-      if ((threadIdx.x & 63) == leader) {
-        float* dst = gatlas + (size_t(kb) * 512 + size_t(kl)) * size_t(C);
-#pragma unroll
-        for (int j = 0; j < CMAX; ++j)
-          if (j < C) unsafeAtomicAdd(dst + j, x[j]);
-      }
-      pending = pending && !mine;
-      pm = __ballot(pending);
-    }
+    // n_blocks * 512 <= 2^31, so a vertex index never reads as kNoRow
+    idx[k] = bid >= 0 ? uint32_t(bid) * 512u + uint32_t(((vz & 7) * 8 + (vy & 7)) * 8 + (vx & 7)) : kNoRow;
+    wk[k] = ((bx ? fr[0] : gr[0]) * (by ? fr[1] : gr[1])) * (bz ? fr[2] : gr[2]);
   }
+  // the cell's coordinates, below 2^11 each
+  const uint32_t key = uint32_t(i0[0]) | (uint32_t(i0[1]) << 11);
+  scatter_cells<CMAX>(gatlas, astride, C, have, key, uint32_t(i0[2]), idx, wk, gco, lane, stage);
 }
 
-template <int DOM, int LMAX, bool PYR, int MODEL>
+// SLOTS: lanes a ray (see march_slots); a workgroup holds 256 / SLOTS rays and
+// writes one partial of the MLP gradient.
+template <int DOM, int LMAX, bool PYR, int MODEL, int SLOTS>
 __global__ void __launch_bounds__(256) backward_kernel(SceneArgs S, int64_t n, const float* __restrict__ O,
                                                        const float* __restrict__ D,
                                                        const float* __restrict__ grad_rgb,
@@ -389,15 +346,17 @@ __global__ void __launch_bounds__(256) backward_kernel(SceneArgs S, int64_t n, c
                                                        const float* __restrict__ ups,
                                                        const float* __restrict__ fcd,
                                                        const float* __restrict__ ffv,
-                                                       float* __restrict__ gtab, float* __restrict__ gatlas,
+                                                       float* __restrict__ gtab, int tstride,
+                                                       float* __restrict__ gatlas, int astride,
                                                        float* __restrict__ partial,
                                                        const float* __restrict__ P, DetRecords det) {
-  __shared__ float sA_all[4][64 * kPad];
-  __shared__ float sB_all[4][64 * kPad];
-  __shared__ float stage_all[4][64 * kStageRow];
+  __shared__ __align__(16) float stage_all[4][kStageFloats];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const int64_t ray = (int64_t(blockIdx.x) * 4 + wave) * 64 + lane;
+  const int slot = lane & (SLOTS - 1);
+  constexpr int kRays = 256 / SLOTS;                     // of the workgroup, at most 64
+  const int ray_in_block = int(threadIdx.x) / SLOTS;
+  const int64_t ray = int64_t(blockIdx.x) * kRays + ray_in_block;
   const bool in_range = ray < n;
   const float* o = O + 3 * (in_range ? ray : 0);
   const float* d = D + 3 * (in_range ? ray : 0);
@@ -413,6 +372,36 @@ __global__ void __launch_bounds__(256) backward_kernel(SceneArgs S, int64_t n, c
   MarchState m;
   float T = 1.0f, cd[3] = {0.f, 0.f, 0.f}, fv[4] = {0.f, 0.f, 0.f, 0.f};
   int ns = 0, reads = 0;
+  // the wave's next samples; false when none of its rays goes on
+  auto next_samples = [&](bool& have, float u[3], int& ks) -> bool {
+    float t;
+    int reads_at;
+    have = march_slots<DOM, PYR, SLOTS>(S, m, slot, reads, u, t, ks, reads_at);
+    return __ballot(have) != 0;
+  };
+  // the transmittance chain over the ray's new samples, in order (e: this
+  // lane's exp(-sigma step)): before = T in front of this lane's sample, used =
+  // the ray had not ended before it; T, ns and the ray's end move on
+  auto advance = [&](bool have, float e, float& before, bool& used, int& my_ns) {
+    const uint32_t bits = slot_bits<SLOTS>(have, lane);
+    bool ended = false;
+    before = T;
+    used = false;
+    each_slot<SLOTS>([&](auto J) {
+      const float ej = slot_value<SLOTS, J>(e);
+      if (((bits >> J) & 1u) && !ended) {
+        if (slot == J) {
+          before = T;
+          used = true;
+          my_ns = ns;
+        }
+        T = T * ej;
+        ++ns;
+        ended = T < S.thr || ns >= S.max_samples;
+      }
+    });
+    if (ended) m.done = true;
+  };
   if (fcd) {
     if (in_range) {
 #pragma unroll
@@ -421,32 +410,45 @@ __global__ void __launch_bounds__(256) backward_kernel(SceneArgs S, int64_t n, c
       for (int j = 0; j < 4; ++j) fv[j] = ffv[ray * 4 + j];
     }
   } else {
-  march_init<DOM>(S, o, d, in_range, m);
-  for (;;) {
-    float u[3], ts;
-    int ks;
-    bool have = march_next<DOM, PYR>(S, m, false, reads, u, ts, ks);
-    if (__ballot(have) == 0) break;
-    if (have) {
-      float f[8];
-      eval_sample<MODEL, DT_F32, LMAX>(S, u, f);
-      const float sigma = exp32(f[0]);
-      const float e = exp32(-(sigma * S.step));
-      const float w = T * (1.0f - e);
-      for (int j = 0; j < 3; ++j) cd[j] = __builtin_fmaf(w, f[1 + j], cd[j]);
-      for (int j = 0; j < 4; ++j) fv[j] = __builtin_fmaf(w, f[4 + j], fv[j]);
-      if (gdist != 0.0f) {
-        const float mid = ((float)ks + 0.5f) * S.step;
-        dP = __builtin_fmaf(w, mid * dW - dS, dP);
-        dQ = __builtin_fmaf(w, w, dQ);
-        dW = dW + w;
-        dS = __builtin_fmaf(w, mid, dS);
+    march_init<DOM>(S, o, d, in_range, m);
+    for (;;) {
+      float u[3] = {0.f, 0.f, 0.f};
+      int ks = 0;
+      bool have;
+      if (!next_samples(have, u, ks)) break;
+      float f[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, e = 1.0f;
+      if (have) {
+        NoSink sink;
+        eval_sample<MODEL, DT_F32, LMAX>(S, u, f, sink);
+        e = exp32(-(exp32(f[0]) * S.step));
       }
-      T = T * e;
-      ++ns;
-      if (T < S.thr || ns >= S.max_samples) m.done = true;
+      float before;
+      bool used;
+      int my_ns = 0;
+      advance(have, e, before, used, my_ns);
+      const float w = before * (1.0f - e);
+      const float mid = ((float)ks + 0.5f) * S.step;
+      const uint32_t bits = slot_bits<SLOTS>(used, lane);
+      // the forward's sums, sample after sample, on every lane of the ray
+      each_slot<SLOTS>([&](auto J) {
+        const float wj = slot_value<SLOTS, J>(w), mj = slot_value<SLOTS, J>(mid);
+        float fj[7];
+#pragma unroll
+        for (int c = 0; c < 7; ++c) fj[c] = slot_value<SLOTS, J>(f[1 + c]);
+        if ((bits >> J) & 1u) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) cd[c] = __builtin_fmaf(wj, fj[c], cd[c]);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) fv[c] = __builtin_fmaf(wj, fj[3 + c], fv[c]);
+          if (gdist != 0.0f) {
+            dP = __builtin_fmaf(wj, mj * dW - dS, dP);
+            dQ = __builtin_fmaf(wj, wj, dQ);
+            dW = dW + wj;
+            dS = __builtin_fmaf(wj, mj, dS);
+          }
+        }
+      });
     }
-  }
   }
 
   float gcd[3], gfv[4];
@@ -518,18 +520,29 @@ __global__ void __launch_bounds__(256) backward_kernel(SceneArgs S, int64_t n, c
 #pragma unroll
     for (int j = 0; j < 4; ++j) gfv[j] = gx[3 + j];
 
-    // ---------------- MLP weight gradients: sums over the wave on MFMA
-    float* sA = sA_all[wave];
-    float* sB = sB_all[wave];
-    float* part = partial + (int64_t(blockIdx.x) * 4 + wave) * kMlpParams;
+    // ---------------- MLP weight gradients: sums over the workgroup's rays on
+    // MFMA by its first wave (a ray's first lane stages its row; rows beyond
+    // kRays, if any, are zero)
+    float* sA = stage_all[0];
+    float* sB = stage_all[0] + 64 * kPad;
+    const bool first = slot == 0;
+    float* part = partial + int64_t(blockIdx.x) * kMlpParams;
     const int qi = lane >> 4, col = lane & 15;
+    if (kRays < 64 && int(threadIdx.x) >= kRays && int(threadIdx.x) < 64) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sA[threadIdx.x * kPad + i] = sB[threadIdx.x * kPad + i] = 0.0f;
+    }
+    float* rowA = sA + ray_in_block * kPad;
+    float* rowB = sB + ray_in_block * kPad;
     // W0 (16 x 7) and b0 (column 7 of x is 1)
+    if (first) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sA[lane * kPad + i] = gz1[i];
+      for (int i = 0; i < 16; ++i) rowA[i] = gz1[i];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) sB[lane * kPad + j] = j < 8 ? x[j < 8 ? j : 0] : 0.0f;
+      for (int j = 0; j < 16; ++j) rowB[j] = j < 8 ? x[j < 8 ? j : 0] : 0.0f;
+    }
     __syncthreads();
-    {
+    if (wave == 0) {
       bf32x4 r = wave_outer_sum(sA, sB, lane);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -540,29 +553,33 @@ __global__ void __launch_bounds__(256) backward_kernel(SceneArgs S, int64_t n, c
     }
     __syncthreads();
     // W1 (16 x 16) and b1
+    if (first) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sA[lane * kPad + i] = gz2[i];
+      for (int i = 0; i < 16; ++i) rowA[i] = gz2[i];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) sB[lane * kPad + j] = h1[j];
+      for (int j = 0; j < 16; ++j) rowB[j] = h1[j];
+    }
     __syncthreads();
-    {
+    if (wave == 0) {
       bf32x4 r = wave_outer_sum(sA, sB, lane);
 #pragma unroll
       for (int q = 0; q < 4; ++q) part[128 + (4 * qi + q) * 16 + col] = r[q];
       if (lane < 16) {
         float a = 0.0f;
-        for (int rr = 0; rr < 64; ++rr) a += sA[rr * kPad + lane];
+        for (int rr = 0; rr < kRays; ++rr) a += sA[rr * kPad + lane];
         part[384 + lane] = a;
       }
     }
     __syncthreads();
     // W2 (3 x 16) and b2
+    if (first) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sA[lane * kPad + i] = i < 3 ? gz[i < 3 ? i : 0] : 0.0f;
+      for (int i = 0; i < 16; ++i) rowA[i] = i < 3 ? gz[i < 3 ? i : 0] : 0.0f;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) sB[lane * kPad + j] = h2[j];
+      for (int j = 0; j < 16; ++j) rowB[j] = h2[j];
+    }
     __syncthreads();
-    {
+    if (wave == 0) {
       bf32x4 r = wave_outer_sum(sA, sB, lane);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -571,7 +588,7 @@ __global__ void __launch_bounds__(256) backward_kernel(SceneArgs S, int64_t n, c
       }
       if (lane < 3) {
         float a = 0.0f;
-        for (int rr = 0; rr < 64; ++rr) a += sA[rr * kPad + lane];
+        for (int rr = 0; rr < kRays; ++rr) a += sA[rr * kPad + lane];
         part[448 + lane] = a;
       }
     }
@@ -581,90 +598,96 @@ __global__ void __launch_bounds__(256) backward_kernel(SceneArgs S, int64_t n, c
                      (gfv[0] * fv[0] + gfv[1] * fv[1] + gfv[2] * fv[2] + gfv[3] * fv[3]);
 
   // ---------------- pass 2: re-march and scatter
-  // Every lane takes part in each iteration (lanes without a sample carry a
-  // zero gradient) so that coarse levels can merge equal table entries across
-  // the wave before the atomics.
+  // Every lane takes part in each iteration (lanes without a sample carry no
+  // gradient) so that the wave can merge the samples of equal cells.
+  __syncthreads();
   march_init<DOM>(S, o, d, in_range, m);
   T = 1.0f;
   ns = 0;
   float Pc = 0.0f, rW = 0.0f, rS = 0.0f;
   const size_t T_entries = size_t(1) << S.log2T;
+  float* stage = stage_all[wave];
   for (;;) {
-    float u[3] = {0.f, 0.f, 0.f}, ts;
-    int ks;
-    const bool have = march_next<DOM, PYR>(S, m, false, reads, u, ts, ks);
-    if (__ballot(have) == 0) break;
-    float gf[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, wl[LMAX], gff = 0.0f;
+    float u[3] = {0.f, 0.f, 0.f};
+    int ks = 0;
+    bool have;
+    if (!next_samples(have, u, ks)) break;
+    GradSink<LMAX> q;
+    q.gcd = gcd;
+    q.gfv = gfv;
+    float f[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, sigma = 0.0f, e = 1.0f;
     if (have) {
-      float f[8];
-      if constexpr (MODEL == 1) {
-        eval_baked<DT_F32, LMAX>(S, u, f);
-      } else {
-        int32_t idx_unused[LMAX * 8];
-        eval_fused<DT_F32, LMAX, true>(S, u, f, wl, idx_unused);
-      }
-      const float sigma = exp32(f[0]);
-      const float e = exp32(-(sigma * S.step));
-      const float w = T * (1.0f - e);
-      float s = (gcd[0] * f[1] + gcd[1] * f[2] + gcd[2] * f[3]) +
-                (gfv[0] * f[4] + gfv[1] * f[5] + gfv[2] * f[6] + gfv[3] * f[7]);
-      if (gdist != 0.0f) {
-        // dL_dist/dw_i = 2 sum_j w_j |m_i - m_j| + 2/3 step w_i (prefix sums over j < i)
-        const float mid = ((float)ks + 0.5f) * S.step;
-        const float pair = (mid * rW - rS) + ((dS - rS - w * mid) - mid * (dW - rW - w));
-        s = __builtin_fmaf(gdist, 2.0f * pair + (2.0f / 3.0f) * S.step * w, s);
-        rW = rW + w;
-        rS = __builtin_fmaf(w, mid, rS);
-      }
-      Pc = __builtin_fmaf(w, s, Pc);
-      const float Tn = T * e;
-      const float gsig = S.step * (Tn * s - (Stot - Pc));
+      eval_sample<MODEL, DT_F32, LMAX>(S, u, f, q);
+      sigma = exp32(f[0]);
+      e = exp32(-(sigma * S.step));
+    }
+    float before;
+    bool used;
+    int my_ns = 0;
+    advance(have, e, before, used, my_ns);
+    have = used;
+    const float w = before * (1.0f - e);
+    const float scol = (gcd[0] * f[1] + gcd[1] * f[2] + gcd[2] * f[3]) +
+                       (gfv[0] * f[4] + gfv[1] * f[5] + gfv[2] * f[6] + gfv[3] * f[7]);
+    float s = scol;
+    const uint32_t bits = slot_bits<SLOTS>(used, lane);
+    if (gdist != 0.0f) {
+      // dL_dist/dw_i = 2 sum_j w_j |m_i - m_j| + 2/3 step w_i (prefix sums over j < i)
+      const float mid = ((float)ks + 0.5f) * S.step;
+      float myW = rW, myS = rS;
+      each_slot<SLOTS>([&](auto J) {
+        const float wj = slot_value<SLOTS, J>(w), mj = slot_value<SLOTS, J>(mid);
+        if (slot == J) {
+          myW = rW;
+          myS = rS;
+        }
+        if ((bits >> J) & 1u) {
+          rW = rW + wj;
+          rS = __builtin_fmaf(wj, mj, rS);
+        }
+      });
+      const float pair = (mid * myW - myS) + ((dS - myS - w * mid) - mid * (dW - myW - w));
+      s = __builtin_fmaf(gdist, 2.0f * pair + (2.0f / 3.0f) * S.step * w, s);
+    }
+    float myP = Pc;
+    each_slot<SLOTS>([&](auto J) {
+      const float wj = slot_value<SLOTS, J>(w), sj = slot_value<SLOTS, J>(s);
+      if ((bits >> J) & 1u) Pc = __builtin_fmaf(wj, sj, Pc);
+      if (slot == J) myP = Pc;
+    });
+    float gf[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (have) {
+      const float gsig = S.step * (before * e * s - (Stot - myP));
       gf[0] = sigma * gsig;
+#pragma unroll
       for (int j = 0; j < 3; ++j) gf[1 + j] = w * gcd[j];
+#pragma unroll
       for (int j = 0; j < 4; ++j) gf[4 + j] = w * gfv[j];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) gff = __builtin_fmaf(gf[j], f[j], gff);
-      T = Tn;
-      ++ns;
-      if (T < S.thr || ns >= S.max_samples) m.done = true;
-    } else {
-#pragma unroll
-      for (int l = 0; l < LMAX; ++l) wl[l] = 0.0f;
     }
     if constexpr (MODEL == 1) {
-      baked_scatter<LMAX>(S, u, have, gf, gtab, gatlas, stage_all[wave]);
+      baked_scatter<LMAX>(S, u, have, gf, w, q, gtab, tstride, gatlas, astride, lane, stage);
       continue;
     }
-#pragma unroll
-    for (int l = 0; l < LMAX; ++l) {
-      if (l >= S.L) break;
+#pragma unroll 1
+    for (int l = 0; l < S.L; ++l) {
       Corners c;
       level_corners(u, S.N[l], S.Nf[l], S.mask, c);
       float gv[9];
 #pragma unroll
       for (int j = 0; j < 9; ++j) gv[j] = 0.0f;
       if (have) {
-        const void* fb = feat_level<DT_F32>(S.feat, l, S.log2T);
-        float v[8][8];
+        const float wl = exp32(q.a[l] - q.run_max) / q.esum;
+        // dL/df . (v_l - f), the differences first: they are exact or nearly so
+        // where the products would cancel
+        const float dot = __builtin_fmaf(gf[0], q.A[l] - f[0], w * (q.B[l] - scol));
 #pragma unroll
-        for (int k = 0; k < 8; ++k) Store<DT_F32>::feat(fb, c.idx[k], v[k]);
-        float gw = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          float acc = 0.0f;
-#pragma unroll
-          for (int k = 0; k < 8; ++k) acc = __builtin_fmaf(c.w[k], v[k][j], acc);
-          gw = __builtin_fmaf(gf[j], acc, gw);
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) gv[j] = wl[l] * gf[j];
-        gv[8] = wl[l] * (gw - gff);
+        for (int j = 0; j < 8; ++j) gv[j] = wl * gf[j];
+        gv[8] = wl * dot;
       }
-      float* gbase = gtab + (size_t(l) * T_entries) * 9;
       if (det.off) {
         // deterministic mode: every contribution to its own record
         if (have) {
-          const int64_t base = ((det.off[ray] + (ns - 1)) * S.L + l) * 8;
+          const int64_t base = ((det.off[ray] + my_ns) * S.L + l) * 8;
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
             const int64_t rec = base + k;
@@ -675,47 +698,9 @@ __global__ void __launch_bounds__(256) backward_kernel(SceneArgs S, int64_t n, c
             for (int j = 0; j < 9; ++j) det.vals[rec * 9 + j] = c.w[k] * gv[j];
           }
         }
-      } else if (S.N[l] >= NGPRT_BW_SORT_MIN_RES) {
-        // equal entries summed after a sort across the wave; the last lane
-        // of each run issues the atomics
-#pragma unroll 1
-        for (int k = 0; k < 8; ++k) {
-          uint32_t key;
-          float wk;
-          corner_pick(c, k, key, wk);
-          float x[9];
-#pragma unroll
-          for (int j = 0; j < 9; ++j) x[j] = wk * gv[j];
-          const bool tail = wave_sort_merge<9>(key, have, x, lane);
-          scatter_runs<9>(gbase, tail, key, x, lane, stage_all[wave]);
-        }
       } else {
-        // sum equal entries over the wave; one lane issues the atomics
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          bool pending = have;
-          uint64_t pm = __ballot(pending);
-          while (pm) {
-            const int leader = __ffsll((unsigned long long)pm) - 1;
-            const uint32_t key = __shfl(c.idx[k], leader, 64);
-            const bool mine = pending && c.idx[k] == key;
-            float x[9];
-#pragma unroll
-            for (int j = 0; j < 9; ++j) x[j] = mine ? c.w[k] * gv[j] : 0.0f;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-              for (int j = 0; j < 9; ++j) x[j] += __shfl_xor(x[j], off, 64);
-            }
-            if (lane == leader) {
-              float* dst = gbase + size_t(key) * 9;
-#pragma unroll
-              for (int j = 0; j < 9; ++j) unsafeAtomicAdd(dst + j, x[j]);
-            }
-            pending = pending && !mine;
-            pm = __ballot(pending);
-          }
-        }
+        scatter_cells<9>(gtab + (size_t(l) * T_entries) * size_t(tstride), tstride, 9, have, c.key0, c.key1, c.idx,
+                         c.w, gv, lane, stage);
       }
     }
   }
@@ -734,18 +719,80 @@ __global__ void adam_kernel(int64_t n, float* __restrict__ p, const float* __res
   p[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
 }
 
+// Lanes a ray of the backward.  A ray's samples are a serial chain, and at
+// four lanes a ray the chain is a quarter as long and four times the waves
+// share the chip, for a few evaluations past a ray's end; small batches do not
+// fill the chip even so and take sixteen.  Measured (training step, tables
+// 8 x 2^14): 2^18 rays at 1 / 2 / 4 / 8 / 16 lanes a ray 3.70 / 3.15 / 3.17 /
+// 3.83 / 5.41 ms, 2^15 rays 2.14 / 1.25 / 0.97 / 0.95 / 1.25, 2^14 rays 1.93 /
+// 1.27 / 0.90 / 0.82 / 0.86 (0.89 at 4 and 0.76 at 16 with the fill rule of
+// march_slots), 2^10 rays 2.29 / 1.24 / 0.83 / 0.67 / 0.64 ms.
+static int backward_slots(int64_t n) { return n <= 16384 ? 16 : 4; }
+
+static int64_t backward_blocks(int64_t n) {
+  const int64_t rays = 256 / backward_slots(n);          // per workgroup
+  return (n + rays - 1) / rays;
+}
+
 size_t backward_workspace_bytes(int64_t n) {
-  const int64_t n_waves = (n + 255) / 256 * 4;
-  return (size_t(n_waves) + kSumGroups) * kMlpParams * sizeof(float);
+  return (size_t(backward_blocks(n)) + kSumGroups) * kMlpParams * sizeof(float);
 }
 
 static bool is_baked_model(const ngprt_ctx* ctx) { return ctx->desc.feature_model == NGPRT_MODEL_BAKED; }
 
+// Padded gradient rows.  The memory side takes float atomics by 64-byte
+// requests: a 36-byte row on its 36-byte stride costs 1.5 of them on average,
+// a row on a 64-byte line of its own costs one (13.9 and 20.9 G rows a
+// second).  So the scatter goes to rows of 16 floats in the workspace, which
+// are then added to the caller's.
+constexpr int kPadRow = 16;
+constexpr size_t kPadMaxBytes = size_t(1) << 30;
+
+// Whether `rows` rows pay for it: a ray sends some 50 rows a level, so padding
+// saves about 1.1 ns a ray and level, and costs 200 bytes a row to clear, read
+// and add, 44 ps: it pays from about rows / 25 rays on (of a level's rows).  Measured
+// on the step of 2^18 rays, 16 x 2^19 tables: 16.7 -> 15.4 ms.
+static bool pad_pays(int64_t n, int64_t rows_per_level, int64_t rows) {
+  return n >= rows_per_level / 16 && size_t(rows) * kPadRow * sizeof(float) <= kPadMaxBytes;
+}
+
+__global__ void clear_rows_kernel(float4* __restrict__ p, int64_t n) {
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
+// dst[r * C + c] += src[r * kPadRow + c] for the first nv of C channels
+__global__ void add_rows_kernel(const float* __restrict__ src, float* __restrict__ dst, int64_t rows, int C, int nv) {
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= rows * C) return;
+  const int64_t r = i / C;
+  const int c = int(i - r * C);
+  if (c >= nv) return;
+  const float v = src[r * kPadRow + c];
+  if (v != 0.0f) dst[i] += v;
+}
+
+static int launch_add_rows(ngprt_ctx* ctx, const float* src, float* dst, int64_t rows, int C, int nv,
+                           hipStream_t st) {
+  const int64_t blocks = (rows * C + 255) / 256;
+  if (blocks > 0x7FFFFFFF) return fail(ctx, NGPRT_E_SHAPE, "gradient too large for one launch");
+  hipLaunchKernelGGL(add_rows_kernel, dim3(unsigned(blocks)), dim3(256), 0, st, src, dst, rows, C, nv);
+  return check_launch(ctx, "add_rows_kernel");
+}
+
 int launch_backward(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, const float* grad_rgb,
                     const float* grad_dist, const float* ups, const float* fcd, const float* ffv,
                     float* gtab, float* gatlas, float* gmlp, hipStream_t st) {
-  if ((n + 255) / 256 > 0x7FFFFFFF) return fail(ctx, NGPRT_E_SHAPE, "too many rays for one launch");
-  const size_t need = backward_workspace_bytes(n);
+  if (backward_blocks(n) > 0x7FFFFFFF) return fail(ctx, NGPRT_E_SHAPE, "too many rays for one launch");
+  const ngprt_desc& ds = ctx->desc;
+  const bool baked = is_baked_model(ctx);
+  const size_t base = (backward_workspace_bytes(n) + 255) / 256 * 256;
+  const int64_t trows = int64_t(ds.n_levels) * ctx->T, arows = baked ? ctx->n_blocks * 512 : 0;
+  const bool tpad = !ctx->det_grad && pad_pays(n, ctx->T, trows);
+  const bool apad = !ctx->det_grad && arows > 0 && pad_pays(n, arows, arows);
+  const size_t tbytes = tpad ? size_t(trows) * kPadRow * sizeof(float) : 0;
+  const size_t abytes = apad ? size_t(arows) * kPadRow * sizeof(float) : 0;
+  const size_t need = base + tbytes + abytes;
   if (need > ctx->ws_bytes) {
     if (ctx->ws) (void)hipFreeAsync(ctx->ws, st);
     ctx->ws = nullptr;
@@ -756,61 +803,74 @@ int launch_backward(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, c
     }
     ctx->ws_bytes = need;
   }
+  float* partial = reinterpret_cast<float*>(ctx->ws);
   if (ctx->det_grad) {
-    if (is_baked_model(ctx))
-      return fail(ctx, NGPRT_E_UNSUPPORTED, "deterministic gradients are built for the hash model");
-    return launch_backward_det(ctx, n, o, d, grad_rgb, grad_dist, ups, fcd, ffv, gtab, gmlp,
-                               reinterpret_cast<float*>(ctx->ws), st);
+    if (baked) return fail(ctx, NGPRT_E_UNSUPPORTED, "deterministic gradients are built for the hash model");
+    return launch_backward_det(ctx, n, o, d, grad_rgb, grad_dist, ups, fcd, ffv, gtab, gmlp, partial, st);
   }
-  return launch_backward_ws(ctx, n, o, d, grad_rgb, grad_dist, ups, fcd, ffv, gtab, gatlas, gmlp,
-                            reinterpret_cast<float*>(ctx->ws), st);
+  float* tws = tpad ? reinterpret_cast<float*>(reinterpret_cast<char*>(ctx->ws) + base) : nullptr;
+  float* aws = apad ? reinterpret_cast<float*>(reinterpret_cast<char*>(ctx->ws) + base + tbytes) : nullptr;
+  if (tbytes + abytes > 0) {
+    const int64_t n4 = int64_t((tbytes + abytes) / sizeof(float4));
+    hipLaunchKernelGGL(clear_rows_kernel, dim3(unsigned((n4 + 255) / 256)), dim3(256), 0, st,
+                       reinterpret_cast<float4*>(tpad ? tws : aws), n4);
+    int rc = check_launch(ctx, "clear_rows_kernel");
+    if (rc) return rc;
+  }
+  const int C = 8 + 2 * ds.n_levels;                      // atlas channels of the baked model
+  int rc = launch_backward_ws(ctx, n, o, d, grad_rgb, grad_dist, ups, fcd, ffv, tpad ? tws : gtab,
+                              tpad ? kPadRow : 9, apad ? aws : gatlas, apad ? kPadRow : C, gmlp, partial, st);
+  if (rc == NGPRT_OK && tpad) rc = launch_add_rows(ctx, tws, gtab, trows, 9, baked ? 8 : 9, st);
+  if (rc == NGPRT_OK && apad) rc = launch_add_rows(ctx, aws, gatlas, arows, C, C, st);
+  return rc;
 }
 
 int launch_backward_ws(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, const float* grad_rgb,
                        const float* grad_dist, const float* ups, const float* fcd, const float* ffv,
-                       float* gtab, float* gatlas, float* gmlp, float* partial, hipStream_t st,
-                       const DetRecords& det) {
+                       float* gtab, int tstride, float* gatlas, int astride, float* gmlp, float* partial,
+                       hipStream_t st, const DetRecords& det) {
   SceneArgs S = scene_args(ctx);
-  const int64_t blocks = (n + 255) / 256;
+  const int64_t blocks = backward_blocks(n);
   if (blocks > 0x7FFFFFFF) return fail(ctx, NGPRT_E_SHAPE, "too many rays for one launch");
-  const int64_t n_waves = blocks * 4;
   dim3 g = dim3(unsigned(blocks));
   const bool box = ctx->desc.domain == DOM_BOX;
-#define NGPRT_BW(DOMV, LM, PY, MD)                                                                 \
-  hipLaunchKernelGGL((backward_kernel<DOMV, LM, PY, MD>), g, dim3(256), 0, st, S, n, o, d, grad_rgb,   \
-                     grad_dist, ups, fcd, ffv, gtab, gatlas, partial, ctx->mlp, det)
+  const bool wide = backward_slots(n) == 16;
+#define NGPRT_BW_S(DOMV, LM, PY, MD, SL)                                                               \
+  hipLaunchKernelGGL((backward_kernel<DOMV, LM, PY, MD, SL>), g, dim3(256), 0, st, S, n, o, d, grad_rgb, \
+                     grad_dist, ups, fcd, ffv, gtab, tstride, gatlas, astride, partial, ctx->mlp, det)
+#define NGPRT_BW(DOMV, LM, PY, MD)          \
+  if (wide) NGPRT_BW_S(DOMV, LM, PY, MD, 16); \
+  else NGPRT_BW_S(DOMV, LM, PY, MD, 4)
+#define NGPRT_BW_DOM(LM, PY, MD)         \
+  if (box) {                             \
+    NGPRT_BW(DOM_BOX, LM, PY, MD);       \
+  } else {                               \
+    NGPRT_BW(DOM_CONTRACT, LM, PY, MD);  \
+  }
   if (S.model == NGPRT_MODEL_BAKED) {
-    // L <= 2 fine levels: coarse rows of at most 12 channels, so the wave
-    // sums in the coarse scatter carry 12 values instead of 16
-    if (S.L <= 2) {
-      if (S.pyr_n > 0) {
-        if (box) NGPRT_BW(DOM_BOX, 2, true, 1);
-        else NGPRT_BW(DOM_CONTRACT, 2, true, 1);
-      } else {
-        if (box) NGPRT_BW(DOM_BOX, 2, false, 1);
-        else NGPRT_BW(DOM_CONTRACT, 2, false, 1);
-      }
+    // L <= 2 fine levels: coarse rows of at most 12 channels
+    if (S.L <= 2 && S.pyr_n > 0) {
+      NGPRT_BW_DOM(2, true, 1)
+    } else if (S.L <= 2) {
+      NGPRT_BW_DOM(2, false, 1)
     } else if (S.pyr_n > 0) {
-      if (box) NGPRT_BW(DOM_BOX, 4, true, 1);
-      else NGPRT_BW(DOM_CONTRACT, 4, true, 1);
+      NGPRT_BW_DOM(4, true, 1)
     } else {
-      if (box) NGPRT_BW(DOM_BOX, 4, false, 1);
-      else NGPRT_BW(DOM_CONTRACT, 4, false, 1);
+      NGPRT_BW_DOM(4, false, 1)
     }
   } else if (S.pyr_n > 0) {
-    if (box) NGPRT_BW(DOM_BOX, 16, true, 0);
-    else NGPRT_BW(DOM_CONTRACT, 16, true, 0);
+    NGPRT_BW_DOM(16, true, 0)
   } else if (S.L <= 8) {
-    if (box) NGPRT_BW(DOM_BOX, 8, false, 0);
-    else NGPRT_BW(DOM_CONTRACT, 8, false, 0);
+    NGPRT_BW_DOM(8, false, 0)
   } else {
-    if (box) NGPRT_BW(DOM_BOX, 16, false, 0);
-    else NGPRT_BW(DOM_CONTRACT, 16, false, 0);
+    NGPRT_BW_DOM(16, false, 0)
   }
+#undef NGPRT_BW_DOM
 #undef NGPRT_BW
+#undef NGPRT_BW_S
   int rc = check_launch(ctx, "backward_kernel");
   if (rc || ups) return rc;
-  return launch_partial_sums(ctx, partial, n_waves, kMlpParams, partial + size_t(n_waves) * kMlpParams, gmlp, st);
+  return launch_partial_sums(ctx, partial, blocks, kMlpParams, partial + size_t(blocks) * kMlpParams, gmlp, st);
 }
 
 int launch_adam(int64_t n, float* p, const float* g, float* m, float* v, int32_t step, float lr, float b1,

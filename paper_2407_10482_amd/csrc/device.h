@@ -219,8 +219,7 @@ __device__ __forceinline__ void level_corners(const float u[3], int N, float Nf,
 // S = fma(S, scale, e_l) and N_j = fma(e_l, v_l[j], N_j * scale).
 // fused_j = N_j / S, and S >= 1, so no sample's softmax underflows whatever
 // the offset of its logits.  Each corner sum is acc = fma(w_k, v_k, acc)
-// from acc = 0, corners in order.  Optionally the
-// attention weights exp32(a_l - m) / S [L] and corner indices [L][8].
+// from acc = 0, corners in order.
 // When every active lane of the wave samples the same cell of a level (most
 // of the time on the coarse levels: the wave's rays are an 8x8 pixel tile),
 // the eight rows come in once by scalar loads instead of 24 vector loads;
@@ -236,9 +235,45 @@ __device__ __forceinline__ void level_corners(const float u[3], int N, float Nf,
 #define NGPRT_SHARED_CELL 1
 #endif
 
-template <int DT, int LMAX, bool DEBUG = false>
-__device__ __forceinline__ void eval_fused(const SceneArgs& S, const float u[3], float fused[8],
-                                           float* wout = nullptr, int32_t* idxout = nullptr) {
+//
+// A sink takes what a level found beside the fused features: level(l, acc, c)
+// the nine interpolated channels and the corners, done(run_max, esum) the
+// softmax's maximum and sum.  NoSink: nothing (the render).  PointSink: the
+// attention weights exp32(a_l - m) / S [L] and corner indices [L][8].
+struct NoSink {
+  __device__ __forceinline__ void level(int, const float*, const Corners&) {}
+  __device__ __forceinline__ void done(float, float) {}
+  __device__ __forceinline__ void gates(int, float, float, const float*, const Corners&) {}
+};
+
+template <int LMAX>
+struct PointSink {
+  float* w;
+  int32_t* idx;
+  int L;
+  __device__ __forceinline__ void level(int l, const float* acc, const Corners& c) {
+    w[l] = acc[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) idx[l * 8 + k] = int32_t(c.idx[k]);
+  }
+  __device__ __forceinline__ void done(float run_max, float esum) {
+#pragma unroll
+    for (int l = 0; l < LMAX; ++l)
+      if (l < L) w[l] = exp32(w[l] - run_max) / esum;
+  }
+  __device__ __forceinline__ void gates(int l, float gw, float, const float*, const Corners& c) {
+#pragma unroll
+    for (int q = 0; q < LMAX; ++q)
+      if (q == l) {
+        w[q] = gw;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) idx[q * 8 + k] = int32_t(c.idx[k]);
+      }
+  }
+};
+
+template <int DT, int LMAX, class Sink>
+__device__ __forceinline__ void eval_fused(const SceneArgs& S, const float u[3], float fused[8], Sink& sink) {
   float run_max = -__int_as_float(0x7F800000), esum = 0.0f, num0 = 0.0f;
   float num[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   // a rolled level loop: per-level constants come in by scalar loads instead
@@ -323,22 +358,14 @@ __device__ __forceinline__ void eval_fused(const SceneArgs& S, const float u[3],
       num0 = __builtin_fmaf(e, acc[0], num0 * sc);
 #pragma unroll
       for (int j = 0; j < 7; ++j) num[j] = __builtin_fmaf(e, acc[1 + j], num[j] * sc);
-      if (DEBUG) {
-        wout[l] = a;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) idxout[l * 8 + k] = int32_t(c.idx[k]);
-      }
+      sink.level(l, acc, c);
     }
   }
   fused[0] = num0 / esum;
   const float inv = 1.0f / esum;
 #pragma unroll
   for (int j = 0; j < 7; ++j) fused[1 + j] = num[j] * inv;
-  if (DEBUG) {
-#pragma unroll
-    for (int l = 0; l < LMAX; ++l)
-      if (l < S.L) wout[l] = exp32(wout[l] - run_max) / esum;
-  }
+  sink.done(run_max, esum);
 }
 
 // ---------------------------------------------------------------------------
@@ -361,9 +388,10 @@ __device__ __forceinline__ float sigmoid32(float a) { return 1.0f / (1.0f + exp3
 // invariant parameters, SUM): level l's two gate parameters are coarse
 // channel S.gidx[l][m] or, where that is -1, the constant S.gconst[l][m];
 // rows may then be 8 floats.
-template <int DT, int LMAX, bool DEBUG = false, bool GEN = false>
-__device__ __forceinline__ void eval_baked(const SceneArgs& S, const float u[3], float fused[8],
-                                           float* wout = nullptr, int32_t* idxout = nullptr) {
+// The sink's gates(l, g_omega, g_beta, acc, c): the level's gates, its eight
+// interpolated channels and its corners.
+template <int DT, int LMAX, bool GEN, class Sink>
+__device__ __forceinline__ void eval_baked(const SceneArgs& S, const float u[3], float fused[8], Sink& sink) {
   static_assert(LMAX <= 4, "the coarse row holds at most 16 channels");
   constexpr int CMAX = 8 + 2 * LMAX;
   int i0[3];
@@ -465,15 +493,7 @@ __device__ __forceinline__ void eval_baked(const SceneArgs& S, const float u[3],
       f0 = __builtin_fmaf(gw, acc[0], f0);
 #pragma unroll
       for (int j = 0; j < 7; ++j) fc[j] = __builtin_fmaf(gb, acc[1 + j], fc[j]);
-      if (DEBUG) {
-#pragma unroll
-        for (int q = 0; q < LMAX; ++q)
-          if (q == l) {
-            wout[q] = gw;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) idxout[q * 8 + k] = int32_t(c.idx[k]);
-          }
-      }
+      sink.gates(l, gw, gb, acc, c);
     }
   }
   fused[0] = f0;
@@ -483,13 +503,12 @@ __device__ __forceinline__ void eval_baked(const SceneArgs& S, const float u[3],
 
 // One sample's fused deferred feature under the scene's feature model.
 // MODEL: bit 0 = baked, bit 2 = its ablation aggregations (GEN).
-template <int MODEL, int DT, int LMAX, bool DEBUG = false>
-__device__ __forceinline__ void eval_sample(const SceneArgs& S, const float u[3], float fused[8],
-                                            float* wout = nullptr, int32_t* idxout = nullptr) {
+template <int MODEL, int DT, int LMAX, class Sink>
+__device__ __forceinline__ void eval_sample(const SceneArgs& S, const float u[3], float fused[8], Sink& sink) {
   if constexpr ((MODEL & 1) != 0)
-    eval_baked<DT, LMAX, DEBUG, (MODEL & 4) != 0>(S, u, fused, wout, idxout);
+    eval_baked<DT, LMAX, (MODEL & 4) != 0>(S, u, fused, sink);
   else
-    eval_fused<DT, LMAX, DEBUG>(S, u, fused, wout, idxout);
+    eval_fused<DT, LMAX>(S, u, fused, sink);
 }
 
 }  // namespace ngprt

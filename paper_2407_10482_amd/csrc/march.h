@@ -13,6 +13,8 @@
 // lattice points are exactly those an exhaustive occupancy march samples.
 #pragma once
 
+#include <type_traits>
+
 #include "device.h"
 
 namespace ngprt {
@@ -330,7 +332,7 @@ constexpr int kAhead = 8;
 
 struct SampleRing {
   float* t;             // this wave's slab: kAhead * 64 lattice t
-  int32_t* reads;       // grid reads of the ray up to and including the entry's
+  int32_t* reads;       // grid reads of the ray up to and including the entry's (NULL: not kept)
   int32_t* k;           // lattice index (NULL: not kept)
   int head, count;
 };
@@ -339,7 +341,7 @@ constexpr int kRingWords = kAhead * 64;
 
 // March until every lane that can still find a sample has one in its ring
 // (or no ray of the wave goes on).  All 64 lanes must call it together.
-template <int DOM, bool PYR, bool LO, bool KEEP_K>
+template <int DOM, bool PYR, bool LO, bool KEEP_K, bool KEEP_READS = true>
 __device__ __forceinline__ void march_ahead(const SceneArgs& S, MarchState& m, bool naive, int& reads,
                                             SampleRing& q, int lane) {
   while (__ballot(!m.done && q.count == 0) != 0) {
@@ -349,7 +351,7 @@ __device__ __forceinline__ void march_ahead(const SceneArgs& S, MarchState& m, b
       if (march_step<DOM, PYR, LO>(S, m, naive, reads, u, ts, ks)) {
         const int at = ((q.head + q.count) & (kAhead - 1)) * 64 + lane;
         q.t[at] = ts;
-        q.reads[at] = reads;
+        if (KEEP_READS) q.reads[at] = reads;
         if (KEEP_K) q.k[at] = ks;
         ++q.count;
       }
@@ -357,14 +359,58 @@ __device__ __forceinline__ void march_ahead(const SceneArgs& S, MarchState& m, b
   }
 }
 
-// Advance this lane's march to its next occupied lattice point.  Returns
-// true with (u, ts, ks) set when a sample was found.
-template <int DOM, bool PYR, bool LO = false>
-__device__ __forceinline__ bool march_next(const SceneArgs& S, MarchState& m, bool naive,
-                                           int& reads, float u[3], float& ts, int& ks) {
-  while (!m.done)
-    if (march_step<DOM, PYR, LO>(S, m, naive, reads, u, ts, ks)) return true;
-  return false;
+// Rays spread over S neighbouring lanes (S = 1: a lane a ray): the lanes of a
+// ray march alike and take one each of its next S samples.  Values of slot J's
+// lane reach the ray's other lanes by a swizzle within the group.
+template <int S, int J>
+__device__ __forceinline__ float slot_value(float v) {
+  if constexpr (S == 1) return v;
+  else return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), (J << 5) | (0x1F & ~(S - 1))));
+}
+
+// the group's slots whose b is set, as bits 0 .. S - 1 (the whole wave calls it)
+template <int S>
+__device__ __forceinline__ uint32_t slot_bits(bool b, int lane) {
+  if constexpr (S == 1) return b ? 1u : 0u;
+  else return uint32_t(__ballot(b) >> (lane & ~(S - 1))) & ((1u << S) - 1u);
+}
+
+// f(integral_constant<int, J>) for the slots in order
+template <int S, int J = 0, class F>
+__device__ __forceinline__ void each_slot(F&& f) {
+  f(std::integral_constant<int, J>{});
+  if constexpr (J + 1 < S) each_slot<S, J + 1>(f);
+}
+
+// The next samples of the wave's 64 / S rays, one a lane, in slot order: the
+// wave marches until every ray that goes on has one, then at most 2 S steps
+// more to fill the other slots (neighbouring samples are a step apart; a ray in
+// a longer gap is not waited for).  Returns whether this lane has a sample.
+template <int DOM, bool PYR, int S>
+__device__ __forceinline__ bool march_slots(const SceneArgs& A, MarchState& m, int slot, int& reads, float u[3],
+                                            float& ts, int& ks, int& reads_at) {
+  int found = 0;
+  bool have = false;
+  for (int fill = 0;;) {
+    if (__ballot(!m.done && found < S) == 0) break;
+    if (__ballot(!m.done && found == 0) == 0 && ++fill > 2 * S) break;
+    if (!m.done && found < S) {
+      float v[3], t;
+      int k;
+      if (march_step<DOM, PYR, false>(A, m, false, reads, v, t, k)) {
+        if (found == slot) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) u[a] = v[a];
+          ts = t;
+          ks = k;
+          reads_at = reads;
+          have = true;
+        }
+        ++found;
+      }
+    }
+  }
+  return have;
 }
 
 }  // namespace ngprt

@@ -248,7 +248,8 @@ render_kernel(SceneArgs S, int64_t n, const float* __restrict__ O,
     }
     if (have) {
       float f[8];
-      eval_sample<MODEL & 5, DT, LMAX>(S, u, f);
+      NoSink sink;
+      eval_sample<MODEL & 5, DT, LMAX>(S, u, f, sink);
       const float sigma = exp32(f[0]);
       const float e = exp32(-(sigma * S.step));
       const float alpha = 1.0f - e;
@@ -330,7 +331,8 @@ __global__ void __launch_bounds__(256) eval_points_kernel(SceneArgs S, int64_t n
   for (int a = 0; a < 3; ++a) u[a] = (p[a] - S.lo) * S.inv_ext;
   float f[8], w[LMAX];
   int32_t id[LMAX * 8];
-  eval_sample<MODEL, DT, LMAX, true>(S, u, f, w, id);
+  PointSink<LMAX> sink{w, id, S.L};
+  eval_sample<MODEL, DT, LMAX>(S, u, f, sink);
   if (fused)
     for (int j = 0; j < 8; ++j) fused[i * 8 + j] = f[j];
   if (weights)
