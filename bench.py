@@ -26,7 +26,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 # sources whose change invalidates hardware counters taken on the render kernel
 KERNEL_SOURCES = ["paper_2407_10482_amd/csrc/" + f for f in
-                  ("render.hip", "device.h", "march.h", "internal.h")] + ["paper_2407_10482_amd/build.py"]
+                  ("render.hip", "render_kernel.h", "render_plain.hip", "device.h", "march.h", "internal.h")] + ["paper_2407_10482_amd/build.py"]
 BYTES_PER_ENTRY = {0: 36, 1: 18, 2: 9}     # 8 feature channels + 1 logit per entry
 DTYPE_NAME = {0: "f32", 1: "bf16", 2: "fp8"}
 AGG_NAME = {"separate_v": "sigmoid-gated separate attention (Separate-Att (V))",

@@ -64,3 +64,54 @@ def test_samples_found_ahead(domain, max_samples):
         assert np.array_equal(out["n_samples"].cpu().numpy(), ref.n_samples)
         assert np.array_equal(out["n_reads"].cpu().numpy(), ref.n_reads)
         assert np.abs(out["rgb"].cpu().numpy() - ref.rgb).max() < 1e-5
+
+
+# 32,768 rays and fewer take sixteen lanes a ray, more take the ring: the same
+# bits either way, so each side checks the other (and the oracle checks the
+# small one above and in the parity tests)
+@pytest.mark.parametrize("name,dtype", [("tiny", 0), ("tiny", 1), ("tiny", 2), ("tiny_pyramid", 0), ("baked_tiny", 0),
+                                        ("baked_tiny_l3", 1), ("paper_tiny", 0), ("baked_tiny_sum", 0)])
+def test_small_launches_match_large_ones(name, dtype):
+    import torch
+    from helpers import gpu_renderer, scene_and_dist
+    print(f"[small launches {name} {dtype}]", flush=True)
+    cfg = scene_and_dist(name, dtype)[0].cfg
+    cams = synth.random_sphere_cameras(9, 1.0, seed=77)
+    o, d, _ = synth.scene_rays(cfg, cams=cams, width=64, height=64)
+    o, d = to_gpu(o[:32769], d[:32769])
+    d[11] = float("nan")
+    r = gpu_renderer(name, dtype)
+
+    def render(n, labels):
+        out = r.alloc_outputs(n, labels=labels)
+        if labels:
+            out["dist_loss"] = torch.empty((n,), device="cuda")
+        return r.render(o[:n].contiguous(), d[:n].contiguous(), out=out)
+    for labels in (False, True):
+        want = render(32769, labels)
+        assert int(want["n_samples"].max()) > 16          # rays of more than one round of sixteen
+        for n in (1, 15, 16, 17, 4099, 32768):
+            got = render(n, labels)
+            for k, v in got.items():
+                assert torch.equal(v.view(torch.int32), want[k][:n].contiguous().view(torch.int32)), (n, labels, k)
+
+
+@pytest.mark.parametrize("domain", ["box", "contract"])
+def test_ring_on_slabs(domain):
+    """The slab scene's gaps through the one-lane kernel (a launch above the
+    small ones), against the small launch of the same rays."""
+    import torch
+    from paper_2407_10482_amd.renderer import Renderer
+    print(f"[ring on slabs {domain}]", flush=True)
+    for cap in (7, 8, 9, 1024):
+        sc = _slab_scene(domain, cap)
+        rng = np.random.default_rng(5)
+        n = 32800
+        o, d = to_gpu(rng.uniform(-1.2, 1.2, size=(n, 3)).astype(np.float32),
+                      rng.normal(size=(n, 3)).astype(np.float32))
+        r = Renderer.from_config(sc.cfg)
+        r.load_scene(*to_gpu(sc.tables, sc.occ, sc.mlp))
+        whole = r.render(o, d)
+        part = r.render(o[:4000].contiguous(), d[:4000].contiguous())
+        for k, v in part.items():
+            assert torch.equal(v.view(torch.int32), whole[k][:4000].contiguous().view(torch.int32)), (cap, k)
