@@ -209,7 +209,6 @@ void ngprt_destroy(ngprt_ctx* ctx) {
   if (ctx->mlp) (void)hipFree(ctx->mlp);
   if (ctx->ws) (void)hipFree(ctx->ws);
   if (ctx->prop_wb) (void)hipFree(ctx->prop_wb);
-  if (ctx->prop_grad) (void)hipFree(ctx->prop_grad);
   if (ctx->prop_net) (void)hipFree(ctx->prop_net);
   if (ctx->prop_tmp) (void)hipFree(ctx->prop_tmp);
   if (ctx->count_ws) (void)hipFree(ctx->count_ws);

@@ -114,14 +114,13 @@ struct ngprt_ctx {
   float* mlp_rec = nullptr;   // view-dependent MLP: weights in MFMA order [8960]
   void* ws = nullptr;         // workspace (per-wave gradient partials of backward / proposal)
   size_t ws_bytes = 0;
-  void* prop_wb = nullptr;    // proposal weights in bfloat16 [7556]
+  void* prop_wb = nullptr;    // proposal training: the weights as bfloat16 operand tiles [52][64] uint2
   void* prop_net = nullptr;   // loaded proposal network: A-operand tiles [32][64] uint2 + biases [132]
   void* prop_tmp = nullptr;   // the same layout for ngprt_proposal_infer's caller-owned weights
   bool prop_loaded = false;
   void* count_ws = nullptr;   // step auto-tuning: per-block partial sums of sample counts + total
   int vmlp_resident = 0;      // view_mlp_kernel workgroups resident together (0: not yet queried)
   bool det_grad = false;      // table gradients by sorted segment sums instead of atomics
-  void* prop_grad = nullptr;  // proposal gradient [7556] when the caller wants none
   int32_t* cidx = nullptr;    // baked model: block index grid [nb^3]
   float* catlas = nullptr;    // baked model: atlas [n_blocks][512][Cpad]
   int64_t n_blocks = 0;

@@ -5,138 +5,57 @@
 // confidence logit.  Parameters (float32 master, caller-owned, 7556 values):
 // W1[64][48], b1[64], W2[64][64], b2[64], W3[4][64], b3[4].
 //
-// One wave owns 64 rays.  Every product is a 16x16 tile of
-// v_mfma_f32_16x16x16_bf16 (bfloat16 operands, float32 accumulation): the
-// layers as D = W X^T (K = input features), the backward as W^T G^T, and
-// the weight gradients as G^T X with K = the wave's 64 rays.  Activations
-// and gradients live in LDS feature-major ([feature][ray], bfloat16), so the
-// weight-gradient operands are contiguous along K.  Per-wave gradient
-// partials are summed by a second kernel in a fixed order; Adam then updates
-// the float32 master copy.
+// Every product is a 16x16 tile of v_mfma_f32_16x16x16_bf16 (bfloat16
+// operands, float32 accumulation).  Training: a workgroup owns 64 rays, each of
+// its four waves runs 16 of them through the network and back with the
+// activations and gradients chained in registers (as proposal_net.h), then the
+// waves share the weight gradients, products with K = the workgroup's rays of
+// operands left in LDS.  Per-workgroup gradient partials are summed in a fixed
+// order; the last kernel also applies Adam to the float32 master copy.
 #include <hip/hip_runtime.h>
+
+#include <cmath>
 
 #include "device.h"
 #include "internal.h"
 #include "proposal_net.h"
+#include "reduce.h"
 
 namespace ngprt {
-
-typedef float pf32x4 __attribute__((ext_vector_type(4)));
-typedef short pbf16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kPIn = 48, kPH = 64, kPOut = 4;
 constexpr int kPW1 = 0, kPB1 = 3072, kPW2 = 3136, kPB2 = 7232, kPW3 = 7296, kPB3 = 7552;
 constexpr int kPParams = 7556;
 constexpr int kPPartial = kPParams + 1;          // + loss
 
-struct PropLds {
-  uint16_t enc[kPIn * 64];     // [feature][ray]
-  uint16_t h1[kPH * 64];
-  uint16_t h2[kPH * 64];
-  float out[kPOut * 64];
-  uint16_t gout[16 * 64];      // rows 4..15 zero
-  uint16_t gz2[kPH * 64];
-  uint16_t gz1[kPH * 64];
-};
-
-// D(16x16) += sum_kc A[i][16kc + k] B[16kc + k][j]; fa(i, k), fb(k, j) return bf16 bits.
-template <class FA, class FB>
-__device__ __forceinline__ pf32x4 mm_tile(int n_kc, FA fa, FB fb, int lane) {
-  const int i = lane & 15, s = lane >> 4;
-  pf32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int kc = 0; kc < n_kc; ++kc) {
-    pbf16x4 a, b;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int k = kc * 16 + 4 * s + e;
-      a[e] = (short)fa(i, k);
-      b[e] = (short)fb(k, i);
-    }
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
-  }
-  return acc;
-}
-
-// sum over the 16 lanes that share (lane >> 4)
-__device__ __forceinline__ float sum16(float v) {
-#pragma unroll
-  for (int off = 1; off < 16; off <<= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
-__device__ __forceinline__ float sum64(float v) {
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
-// Forward of the wave's 64 rays into L.out (float32 outputs before the sigmoid).
-__device__ __forceinline__ void prop_forward(PropLds& L, const float* __restrict__ P,
-                                             const uint16_t* __restrict__ Wb, const float* o,
-                                             const float* d, bool in_range, int lane) {
-  // Fourier features of this lane's ray
-  float r[6];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    r[j] = in_range ? o[j] : 0.0f;
-    r[3 + j] = in_range ? d[j] : 0.0f;
-  }
-#pragma unroll
-  for (int j = 0; j < 6; ++j) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float a = float(1 << k) * r[j];
-      L.enc[(8 * j + 2 * k) * 64 + lane] = bf16_rne(sinpif(a));
-      L.enc[(8 * j + 2 * k + 1) * 64 + lane] = bf16_rne(cospif(a));
-    }
-  }
-  __syncthreads();
-  const int s = lane >> 4, col = lane & 15;
-  // layer 1: h1 = relu(W1 enc + b1)
-  for (int mt = 0; mt < 4; ++mt)
-    for (int nt = 0; nt < 4; ++nt) {
-      pf32x4 acc = mm_tile(
-          3, [&](int i, int k) { return Wb[kPW1 + (mt * 16 + i) * kPIn + k]; },
-          [&](int k, int j) { return L.enc[k * 64 + nt * 16 + j]; }, lane);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int row = mt * 16 + 4 * s + q;
-        L.h1[row * 64 + nt * 16 + col] = bf16_rne(fmaxf(acc[q] + P[kPB1 + row], 0.0f));
-      }
-    }
-  __syncthreads();
-  // layer 2
-  for (int mt = 0; mt < 4; ++mt)
-    for (int nt = 0; nt < 4; ++nt) {
-      pf32x4 acc = mm_tile(
-          4, [&](int i, int k) { return Wb[kPW2 + (mt * 16 + i) * kPH + k]; },
-          [&](int k, int j) { return L.h1[k * 64 + nt * 16 + j]; }, lane);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int row = mt * 16 + 4 * s + q;
-        L.h2[row * 64 + nt * 16 + col] = bf16_rne(fmaxf(acc[q] + P[kPB2 + row], 0.0f));
-      }
-    }
-  __syncthreads();
-  // layer 3 (4 outputs, rows 4..15 of the tile zero)
-  for (int nt = 0; nt < 4; ++nt) {
-    pf32x4 acc = mm_tile(
-        4, [&](int i, int k) { return i < kPOut ? Wb[kPW3 + i * kPH + k] : (uint16_t)0; },
-        [&](int k, int j) { return L.h2[k * 64 + nt * 16 + j]; }, lane);
-    if (s == 0) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) L.out[q * 64 + nt * 16 + col] = acc[q] + P[kPB3 + q];
-    }
-  }
-  __syncthreads();
-}
+// Operand tiles of the backward products beside the kPropTiles of the forward:
+// W3^T (m) at kPropTiles + m, W2^T (m, kc) at kPropTiles + 4 + 4 m + kc; tile t,
+// lane l: W3[4 (l / 16) + e][16 m + l % 16] (rows past the 4 outputs zero) and
+// W2[16 kc + 4 (l / 16) + e][16 m + l % 16], e = 0..3.
+constexpr int kPropTrainTiles = kPropTiles + 4 + 16;
 
 // Float32 master weights -> the A-operand tiles and biases of
 // prop_infer_wave (proposal_net.h): 32 tiles x 64 lanes of four bfloat16,
-// then b1, b2, b3 as float32.
-__global__ void prop_arrange_kernel(const float* __restrict__ P, uint2* __restrict__ tiles,
+// then b1, b2, b3 as float32 (NULL: not wanted).  n_tiles = kPropTrainTiles: the
+// backward's tiles too.
+__global__ void prop_arrange_kernel(const float* __restrict__ P, uint2* __restrict__ tiles, int n_tiles,
                                     float* __restrict__ bias) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= kPropTiles * 64 && t < n_tiles * 64) {
+    const int tile = (t >> 6) - kPropTiles, lane = t & 63;
+    const int i = lane & 15, k0 = 4 * (lane >> 4);
+    uint16_t h[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (tile < 4) {
+        h[e] = k0 + e < kPOut ? bf16_rne(P[kPW3 + (k0 + e) * kPH + 16 * tile + i]) : (uint16_t)0;
+      } else {
+        const int m = (tile - 4) >> 2, kc = (tile - 4) & 3;
+        h[e] = bf16_rne(P[kPW2 + (16 * kc + k0 + e) * kPH + 16 * m + i]);
+      }
+    }
+    tiles[t] = make_uint2(uint32_t(h[0]) | (uint32_t(h[1]) << 16), uint32_t(h[2]) | (uint32_t(h[3]) << 16));
+  }
   if (t < kPropTiles * 64) {
     const int tile = t >> 6, lane = t & 63;
     const int i = lane & 15, k0 = 4 * (lane >> 4);
@@ -156,7 +75,7 @@ __global__ void prop_arrange_kernel(const float* __restrict__ P, uint2* __restri
     for (int e = 0; e < 4; ++e) h[e] = zero ? (uint16_t)0 : bf16_rne(P[base + (zero ? 0 : row) * ld + col + e]);
     tiles[t] = make_uint2(uint32_t(h[0]) | (uint32_t(h[1]) << 16), uint32_t(h[2]) | (uint32_t(h[3]) << 16));
   }
-  if (t < kPropBias) bias[t] = t < 64 ? P[kPB1 + t] : (t < 128 ? P[kPB2 + t - 64] : P[kPB3 + t - 128]);
+  if (bias && t < kPropBias) bias[t] = t < 64 ? P[kPB1 + t] : (t < 128 ? P[kPB2 + t - 64] : P[kPB3 + t - 128]);
 }
 
 // Stand-alone inference: four waves per workgroup, one wave per 64 rays.
@@ -177,36 +96,120 @@ __global__ void __launch_bounds__(256) prop_infer_kernel(int64_t n, const float*
   }
 }
 
+// LDS of a workgroup in training, feature-major ([feature][ray], bfloat16), so
+// that the weight gradients' operands are four consecutive rays; the row pitch
+// spreads the four lane groups of a store over the banks.
+constexpr int kRP = 68;
+struct PropLds {
+  uint16_t enc[kPIn * kRP];
+  uint16_t h1[kPH * kRP];
+  uint16_t h2[kPH * kRP];
+  uint16_t gz2[kPH * kRP];
+  uint16_t gz1[kPH * kRP];
+  uint16_t gout[16 * kRP];     // rows 4..15 zero
+  float sums[4][2 * kPH + 5];  // per wave: db2, db1, db3, loss
+};
+
+// sum over the 16 lanes that share (lane >> 4)
+__device__ __forceinline__ float sum16(float v) {
+#pragma unroll
+  for (int off = 1; off < 16; off <<= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// bfloat16 v[e] of rows row0 + e to column `ray`
+__device__ __forceinline__ void put_rows(uint16_t* a, int row0, int ray, pn_bf16x4 v) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) a[(row0 + e) * kRP + ray] = (uint16_t)v[e];
+}
+
+// four consecutive rays of one row, an operand of the weight gradients
+__device__ __forceinline__ pn_bf16x4 rays4(const uint16_t* a, int row, int ray) {
+  return *reinterpret_cast<const pn_bf16x4*>(a + row * kRP + ray);
+}
+
+// D = sum over the 64 rays of A[i][ray] B[j][ray], rows ra + i of A, rb + j of B
+__device__ __forceinline__ pn_f32x4 outer_rays(const uint16_t* A, int ra, const uint16_t* B, int rb, int lane) {
+  const int i = lane & 15, s = lane >> 4;
+  pn_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kc = 0; kc < 4; ++kc)
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(rays4(A, ra + i, 16 * kc + 4 * s),
+                                                    rays4(B, rb + i, 16 * kc + 4 * s), acc, 0, 0, 0);
+  return acc;
+}
+
 // Labels [n][4]: t_near, t_far, t_term, valid (1/0).  phase 1: pinball
 // losses on t_near (quantile 0.05) and t_far (0.95), squared error on t_term;
 // phase >= 2: + confidence cross-entropy with target = valid and
 // [out0 - margin, out1 + margin] contains [t_near, t_far].  Loss terms are
 // divided by n (the batch).
-__global__ void __launch_bounds__(64) prop_train_kernel(int64_t n, const float* __restrict__ O,
-                                                        const float* __restrict__ D,
-                                                        const float* __restrict__ labels,
-                                                        int phase, float margin,
-                                                        const float* __restrict__ P,
-                                                        const uint16_t* __restrict__ Wb,
-                                                        float* __restrict__ partial) {
-  __shared__ PropLds L;
-  const int lane = threadIdx.x;
-  const int64_t ray = int64_t(blockIdx.x) * 64 + lane;
+// Bound by the latency of its chain of small products (2^14 rays are 256
+// workgroups, one a CU): a wave of 64 rays with every operand gathered from LDS
+// by 2-byte reads took 36.8 us, four waves of 16 rays with the products chained
+// in registers 16.7 us.
+__global__ void __launch_bounds__(256) prop_train_kernel(int64_t n, const float* __restrict__ O,
+                                                         const float* __restrict__ D,
+                                                         const float* __restrict__ labels, int phase, float margin,
+                                                         const float* __restrict__ P,
+                                                         const uint2* __restrict__ tiles,
+                                                         float* __restrict__ partial) {
+  __shared__ __align__(16) PropLds L;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = lane & 15, s = lane >> 4;
+  const int col = 16 * wave + j;                            // this lane's ray in the workgroup
+  const int64_t ray = int64_t(blockIdx.x) * 64 + col;
   const bool in_range = ray < n;
-  prop_forward(L, P, Wb, O + 3 * (in_range ? ray : 0), D + 3 * (in_range ? ray : 0), in_range, lane);
-  const int s = lane >> 4, col = lane & 15;
   float* part = partial + int64_t(blockIdx.x) * kPPartial;
-  const float inv_n = 1.0f / float(n);
+  // forward (the operand layout is prop_infer_wave's)
+  pn_bf16x4 enc[3], h1[4], h2[4];
+#pragma unroll
+  for (int kc = 0; kc < 3; ++kc) {
+    const int comp = 2 * kc + (s >> 1);
+    const float* src = comp < 3 ? O : D;
+    const float r = in_range ? src[3 * (in_range ? ray : 0) + (comp < 3 ? comp : comp - 3)] : 0.0f;
+    const int k0 = 2 * (s & 1);
+    const float a0 = float(1 << k0) * r, a1 = float(2 << k0) * r;
+    enc[kc] = pn_pack(sinpif(a0), cospif(a0), sinpif(a1), cospif(a1));
+    put_rows(L.enc, 16 * kc + 4 * s, col, enc[kc]);
+  }
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    pn_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kc = 0; kc < 3; ++kc)
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pn_tile(tiles, m * 3 + kc, lane), enc[kc], acc, 0, 0, 0);
+    const float* b = P + kPB1 + 16 * m + 4 * s;
+    h1[m] = pn_pack(fmaxf(acc[0] + b[0], 0.0f), fmaxf(acc[1] + b[1], 0.0f), fmaxf(acc[2] + b[2], 0.0f),
+                    fmaxf(acc[3] + b[3], 0.0f));
+    put_rows(L.h1, 16 * m + 4 * s, col, h1[m]);
+  }
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    pn_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kc = 0; kc < 4; ++kc)
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pn_tile(tiles, 12 + m * 4 + kc, lane), h1[kc], acc, 0, 0, 0);
+    const float* b = P + kPB2 + 16 * m + 4 * s;
+    h2[m] = pn_pack(fmaxf(acc[0] + b[0], 0.0f), fmaxf(acc[1] + b[1], 0.0f), fmaxf(acc[2] + b[2], 0.0f),
+                    fmaxf(acc[3] + b[3], 0.0f));
+    put_rows(L.h2, 16 * m + 4 * s, col, h2[m]);
+  }
+  pn_f32x4 out = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kc = 0; kc < 4; ++kc)
+    out = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pn_tile(tiles, 28 + kc, lane), h2[kc], out, 0, 0, 0);
 
-  // loss and dL/dout for this lane's ray
+  // loss and dL/dout: the four outputs of a ray are in lane j of the first 16
+  const float inv_n = 1.0f / float(n);
   float go[4] = {0.f, 0.f, 0.f, 0.f};
   float loss = 0.0f;
-  if (in_range) {
+  if (s == 0 && in_range) {
     const float* y = labels + ray * 4;
     const bool valid = y[3] != 0.0f;
     float ov[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) ov[c] = L.out[c * 64 + lane];
+    for (int c = 0; c < 4; ++c) ov[c] = out[c] + P[kPB3 + c];
     if (valid) {
       // t_near: pinball loss at quantile 0.05; t_far: at 0.95; t_term: squared error
       const float r0 = y[0] - ov[0], r1 = y[1] - ov[1], df = ov[2] - y[2];
@@ -222,116 +225,114 @@ __global__ void __launch_bounds__(64) prop_train_kernel(int64_t n, const float* 
       go[3] = (sg - tgt) * inv_n;
     }
   }
-  loss = sum64(loss * inv_n);
-#pragma unroll
-  for (int c = 0; c < 16; ++c) L.gout[c * 64 + lane] = c < 4 ? bf16_rne(go[c < 4 ? c : 0]) : (uint16_t)0;
+  float* sums = L.sums[wave];
   {
+    const float ls = sum16(loss * inv_n);
     float b3[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) b3[c] = sum64(go[c]);
+    for (int c = 0; c < 4; ++c) b3[c] = sum16(go[c]);
     if (lane == 0) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) part[kPB3 + c] = b3[c];
-      part[kPParams] = loss;
+      for (int c = 0; c < 4; ++c) sums[2 * kPH + c] = b3[c];
+      sums[2 * kPH + 4] = ls;
     }
   }
-  __syncthreads();
-  // gz2 = (W3^T gout) * [h2 > 0]
-  for (int mt = 0; mt < 4; ++mt) {
-    float bsum[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int nt = 0; nt < 4; ++nt) {
-      pf32x4 acc = mm_tile(
-          1, [&](int i, int k) { return k < kPOut ? Wb[kPW3 + k * kPH + mt * 16 + i] : (uint16_t)0; },
-          [&](int k, int j) { return L.gout[k * 64 + nt * 16 + j]; }, lane);
+  // B operand of the first backward product: rows 4 s + e, of which 0..3 hold
+  // dL/dout (zero on the lanes of s > 0, as go is)
+  const pn_bf16x4 gout = pn_pack(go[0], go[1], go[2], go[3]);
+  put_rows(L.gout, 4 * s, col, gout);
+  // gz2 = (W3^T gout) * [h2 > 0], gz1 = (W2^T gz2) * [h1 > 0]
+  pn_bf16x4 gz2[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int row = mt * 16 + 4 * s + q, rc = nt * 16 + col;
-        const float g = bf16_to_f32(L.h2[row * 64 + rc]) > 0.0f ? acc[q] : 0.0f;
-        L.gz2[row * 64 + rc] = bf16_rne(g);
-        bsum[q] += g;
-      }
-    }
+  for (int m = 0; m < 4; ++m) {
+    pn_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pn_tile(tiles, kPropTiles + m, lane), gout, acc, 0, 0, 0);
+    float g[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const float t = sum16(bsum[q]);
-      if (col == 0) part[kPB2 + mt * 16 + 4 * s + q] = t;
+      g[q] = bf16_to_f32((uint16_t)h2[m][q]) > 0.0f ? acc[q] : 0.0f;
+      const float t = sum16(g[q]);
+      if (j == 0) sums[16 * m + 4 * s + q] = t;
     }
+    gz2[m] = pn_pack(g[0], g[1], g[2], g[3]);
+    put_rows(L.gz2, 16 * m + 4 * s, col, gz2[m]);
   }
-  __syncthreads();
-  // gz1 = (W2^T gz2) * [h1 > 0]
-  for (int mt = 0; mt < 4; ++mt) {
-    float bsum[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int nt = 0; nt < 4; ++nt) {
-      pf32x4 acc = mm_tile(
-          4, [&](int i, int k) { return Wb[kPW2 + k * kPH + mt * 16 + i]; },
-          [&](int k, int j) { return L.gz2[k * 64 + nt * 16 + j]; }, lane);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int row = mt * 16 + 4 * s + q, rc = nt * 16 + col;
-        const float g = bf16_to_f32(L.h1[row * 64 + rc]) > 0.0f ? acc[q] : 0.0f;
-        L.gz1[row * 64 + rc] = bf16_rne(g);
-        bsum[q] += g;
-      }
-    }
+  for (int m = 0; m < 4; ++m) {
+    pn_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kc = 0; kc < 4; ++kc)
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pn_tile(tiles, kPropTiles + 4 + 4 * m + kc, lane), gz2[kc], acc,
+                                                      0, 0, 0);
+    float g[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const float t = sum16(bsum[q]);
-      if (col == 0) part[kPB1 + mt * 16 + 4 * s + q] = t;
+      g[q] = bf16_to_f32((uint16_t)h1[m][q]) > 0.0f ? acc[q] : 0.0f;
+      const float t = sum16(g[q]);
+      if (j == 0) sums[kPH + 16 * m + 4 * s + q] = t;
     }
+    put_rows(L.gz1, 16 * m + 4 * s, col, pn_pack(g[0], g[1], g[2], g[3]));
   }
   __syncthreads();
-  // weight gradients, K = the wave's rays
-  for (int nt = 0; nt < 4; ++nt) {          // dW3[4][64]
-    pf32x4 acc = mm_tile(
-        4, [&](int i, int k) { return L.gout[i * 64 + k]; },
-        [&](int k, int j) { return L.h2[(nt * 16 + j) * 64 + k]; }, lane);
+  // weight gradients: wave w takes row block w of dW2 and dW1, column block w of dW3
+  {
+    const pn_f32x4 r = outer_rays(L.gout, 0, L.h2, 16 * wave, lane);
     if (s == 0) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) part[kPW3 + q * kPH + nt * 16 + col] = acc[q];
+      for (int q = 0; q < 4; ++q) part[kPW3 + q * kPH + 16 * wave + j] = r[q];
     }
   }
-  for (int mt = 0; mt < 4; ++mt)             // dW2[64][64]
-    for (int nt = 0; nt < 4; ++nt) {
-      pf32x4 acc = mm_tile(
-          4, [&](int i, int k) { return L.gz2[(mt * 16 + i) * 64 + k]; },
-          [&](int k, int j) { return L.h1[(nt * 16 + j) * 64 + k]; }, lane);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) part[kPW2 + (mt * 16 + 4 * s + q) * kPH + nt * 16 + col] = acc[q];
-    }
-  for (int mt = 0; mt < 4; ++mt)             // dW1[64][48]
-    for (int nt = 0; nt < 3; ++nt) {
-      pf32x4 acc = mm_tile(
-          4, [&](int i, int k) { return L.gz1[(mt * 16 + i) * 64 + k]; },
-          [&](int k, int j) { return L.enc[(nt * 16 + j) * 64 + k]; }, lane);
+  for (int nt = 0; nt < 4; ++nt) {
+    const pn_f32x4 r = outer_rays(L.gz2, 16 * wave, L.h1, 16 * nt, lane);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) part[kPW1 + (mt * 16 + 4 * s + q) * kPIn + nt * 16 + col] = acc[q];
-    }
+    for (int q = 0; q < 4; ++q) part[kPW2 + (16 * wave + 4 * s + q) * kPH + 16 * nt + j] = r[q];
+  }
+#pragma unroll
+  for (int nt = 0; nt < 3; ++nt) {
+    const pn_f32x4 r = outer_rays(L.gz1, 16 * wave, L.enc, 16 * nt, lane);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) part[kPW1 + (16 * wave + 4 * s + q) * kPIn + 16 * nt + j] = r[q];
+  }
+  // the biases' and the loss's sums over the four waves
+  const int t = int(threadIdx.x);
+  if (t < 2 * kPH + 5) {
+    const float a = (L.sums[0][t] + L.sums[1][t]) + (L.sums[2][t] + L.sums[3][t]);
+    part[t < kPH ? kPB2 + t : (t < 2 * kPH ? kPB1 + t - kPH : (t < 2 * kPH + 4 ? kPB3 + t - 2 * kPH : kPParams))] = a;
+  }
 }
 
-__global__ void prop_reduce_kernel(const float* __restrict__ partial, int64_t n_waves,
-                                   float* __restrict__ grad, float* __restrict__ loss) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= kPPartial) return;
+// The groups' sums in order, the loss, and Adam on the float32 weights when m
+// and v are given (the update of adam_kernel).
+__global__ void prop_finish_kernel(const float* __restrict__ tmp, float* __restrict__ grad, float* __restrict__ loss,
+                                   float* __restrict__ p, float* __restrict__ m, float* __restrict__ v, float lr,
+                                   float b1, float b2, float eps, float c1, float c2) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= kPPartial) return;
   float a = 0.0f;
-  for (int64_t w = 0; w < n_waves; ++w) a += partial[w * kPPartial + p];
-  if (p < kPParams) grad[p] = a;
-  else if (loss) loss[0] += a;
+#pragma unroll 16
+  for (int g = 0; g < kSumGroups; ++g) a += tmp[int64_t(g) * kPPartial + i];
+  if (i == kPParams) {
+    if (loss) loss[0] += a;
+    return;
+  }
+  if (grad) grad[i] = a;
+  if (m) {
+    const float mi = b1 * m[i] + (1.0f - b1) * a;
+    const float vi = b2 * v[i] + (1.0f - b2) * a * a;
+    m[i] = mi;
+    v[i] = vi;
+    p[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
+  }
 }
 
-__global__ void prop_cast_kernel(const float* __restrict__ P, uint16_t* __restrict__ Wb) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < kPParams) Wb[p] = bf16_rne(P[p]);
-}
-
-static int ensure_prop_buffers(ngprt_ctx* ctx, int64_t n_waves, hipStream_t st) {
-  // each buffer on its own, so that a failed call leaves nothing half made
-  if ((!ctx->prop_wb &&
-       dev_malloc_async((void**)&ctx->prop_wb, kPParams * sizeof(uint16_t), st) != hipSuccess) ||
-      (!ctx->prop_grad && dev_malloc_async((void**)&ctx->prop_grad, kPParams * sizeof(float), st) != hipSuccess)) {
+static int ensure_prop_buffers(ngprt_ctx* ctx, int64_t n_parts, hipStream_t st) {
+  if (!ctx->prop_wb &&
+      dev_malloc_async((void**)&ctx->prop_wb, size_t(kPropTrainTiles) * 64 * sizeof(uint2), st) != hipSuccess) {
     (void)hipGetLastError();
     return fail(ctx, NGPRT_E_ALLOC, "proposal buffers");
   }
-  const size_t need = size_t(n_waves) * kPPartial * sizeof(float);
+  const size_t need = size_t(n_parts + kSumGroups) * kPPartial * sizeof(float);
   if (need > ctx->ws_bytes) {
     if (ctx->ws) (void)hipFreeAsync(ctx->ws, st);
     ctx->ws = nullptr;
@@ -351,7 +352,8 @@ constexpr size_t kPropNetBytes = size_t(kPropTiles) * 64 * sizeof(uint2) + kProp
 int launch_prop_arrange(ngprt_ctx* ctx, const float* P, void* dst, hipStream_t st) {
   uint2* tiles = reinterpret_cast<uint2*>(dst);
   float* bias = reinterpret_cast<float*>(reinterpret_cast<char*>(dst) + size_t(kPropTiles) * 64 * sizeof(uint2));
-  hipLaunchKernelGGL(prop_arrange_kernel, dim3((kPropTiles * 64 + 255) / 256), dim3(256), 0, st, P, tiles, bias);
+  hipLaunchKernelGGL(prop_arrange_kernel, dim3((kPropTiles * 64 + 255) / 256), dim3(256), 0, st, P, tiles,
+                     kPropTiles, bias);
   return check_launch(ctx, "prop_arrange_kernel");
 }
 
@@ -392,22 +394,26 @@ int launch_prop_train(ngprt_ctx* ctx, int64_t n, const float* o, const float* d,
   if (blocks > (int64_t(1) << 24)) return fail(ctx, NGPRT_E_SHAPE, "batch too large");
   int rc = ensure_prop_buffers(ctx, blocks, st);
   if (rc) return rc;
-  hipLaunchKernelGGL(prop_cast_kernel, dim3((kPParams + 255) / 256), dim3(256), 0, st, P,
-                     (uint16_t*)ctx->prop_wb);
-  if ((rc = check_launch(ctx, "prop_cast_kernel"))) return rc;
+  uint2* tiles = reinterpret_cast<uint2*>(ctx->prop_wb);
+  hipLaunchKernelGGL(prop_arrange_kernel, dim3((kPropTrainTiles * 64 + 255) / 256), dim3(256), 0, st, P, tiles,
+                     kPropTrainTiles, nullptr);
+  if ((rc = check_launch(ctx, "prop_arrange_kernel"))) return rc;
   float* partial = reinterpret_cast<float*>(ctx->ws);
-  hipLaunchKernelGGL(prop_train_kernel, dim3(unsigned(blocks)), dim3(64), 0, st, n, o, d, labels, phase,
-                     margin, P, (const uint16_t*)ctx->prop_wb, partial);
+  hipLaunchKernelGGL(prop_train_kernel, dim3(unsigned(blocks)), dim3(256), 0, st, n, o, d, labels, phase, margin, P,
+                     tiles, partial);
   if ((rc = check_launch(ctx, "prop_train_kernel"))) return rc;
-  float* grad = grad_out ? grad_out : reinterpret_cast<float*>(ctx->prop_grad);
-  hipLaunchKernelGGL(prop_reduce_kernel, dim3((kPPartial + 255) / 256), dim3(256), 0, st, partial, blocks,
-                     grad, loss);
-  if ((rc = check_launch(ctx, "prop_reduce_kernel"))) return rc;
-  if (m && v) {
-    rc = launch_adam(kPParams, P, grad, m, v, step, lr, 0.9f, 0.99f, 1e-8f, st);
-    if (rc) return fail(ctx, rc, "adam");
-  }
-  return NGPRT_OK;
+  // one thread a parameter over all partials took 59 us at 2^14 rays; 64 groups
+  // of partials, then the groups, 8 us with Adam
+  float* tmp = partial + size_t(blocks) * kPPartial;
+  hipLaunchKernelGGL(partial_group_sums_kernel, dim3((kPPartial + 255) / 256, kSumGroups), dim3(256), 0, st, partial,
+                     blocks, kPPartial, tmp);
+  if ((rc = check_launch(ctx, "partial_group_sums_kernel"))) return rc;
+  const bool adam = m && v;
+  const double c1 = adam ? 1.0 / (1.0 - std::pow(double(0.9f), double(step))) : 1.0;
+  const double c2 = adam ? 1.0 / (1.0 - std::pow(double(0.99f), double(step))) : 1.0;
+  hipLaunchKernelGGL(prop_finish_kernel, dim3((kPPartial + 255) / 256), dim3(256), 0, st, tmp, grad_out, loss, P,
+                     adam ? m : nullptr, adam ? v : nullptr, lr, 0.9f, 0.99f, 1e-8f, float(c1), float(c2));
+  return check_launch(ctx, "prop_finish_kernel");
 }
 
 }  // namespace ngprt
