@@ -224,6 +224,34 @@ __device__ __forceinline__ bool read_voxel(const SceneArgs& S, MarchState& m, bo
   return occupied;
 }
 
+// Contracted domain: the image p of the lattice point at tcur, the advance dt of
+// t to the next one, and whether the ray ends there.
+__device__ __forceinline__ void contract_point(const SceneArgs& S, const MarchState& m, float tcur, float p[3],
+                                               float& dt, bool& end) {
+  float x[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) x[a] = m.o[a] + tcur * m.d[a];
+  const float r2 = (x[0] * x[0] + x[1] * x[1]) + x[2] * x[2];
+  end = end || !isfinite(r2);
+  // inside the unit ball x is its own image and |J d| = |d|: the quotient
+  // step / |J d| taken once per ray
+  float s = 1.0f;
+  dt = m.dt_in;
+  if (r2 > 1.0f) {
+    const float r = sqrtf(r2);
+    const float inv_r = 1.0f / r;
+    s = (2.0f - inv_r) * inv_r;
+    const float xd = ((x[0] * m.d[0] + x[1] * m.d[1]) + x[2] * m.d[2]) * inv_r;
+    end = end || (inv_r < S.step && xd >= 0.0f);
+    const float perp2 = fmaxf(m.dn2 - xd * xd, 0.0f);
+    const float rad = xd * (inv_r * inv_r);
+    const float jn = sqrtf((s * s) * perp2 + rad * rad);
+    dt = S.step / jn;
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) p[a] = s * x[a];
+}
+
 // Visit this lane's next lattice point.  Returns true with (u, ts, ks) set
 // when it is a sample (its voxel is occupied); sets m.done when the ray leaves
 // the domain.  Call it only while !m.done.
@@ -250,27 +278,8 @@ __device__ __forceinline__ bool march_step(const SceneArgs& S, MarchState& m, bo
     for (int a = 0; a < 3; ++a) p[a] = m.o[a] + tcur * m.d[a];
   } else {
     tcur = m.t;
-    float x[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) x[a] = m.o[a] + tcur * m.d[a];
-    const float r2 = (x[0] * x[0] + x[1] * x[1]) + x[2] * x[2];
-    end = end || !isfinite(r2);
-    // inside the unit ball x is its own image and |J d| = |d|: the quotient
-    // step / |J d| taken once per ray
-    float s = 1.0f, dt = m.dt_in;
-    if (r2 > 1.0f) {
-      const float r = sqrtf(r2);
-      const float inv_r = 1.0f / r;
-      s = (2.0f - inv_r) * inv_r;
-      const float xd = ((x[0] * m.d[0] + x[1] * m.d[1]) + x[2] * m.d[2]) * inv_r;
-      end = end || (inv_r < S.step && xd >= 0.0f);
-      const float perp2 = fmaxf(m.dn2 - xd * xd, 0.0f);
-      const float rad = xd * (inv_r * inv_r);
-      const float jn = sqrtf((s * s) * perp2 + rad * rad);
-      dt = S.step / jn;
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) p[a] = s * x[a];
+    float dt;
+    contract_point(S, m, tcur, p, dt, end);
     m.t = tcur + dt;
     // points in the known-empty ball take no read
     const float e0 = p[0] - m.bc[0], e1 = p[1] - m.bc[1], e2 = p[2] - m.bc[2];
@@ -388,31 +397,125 @@ __device__ __forceinline__ void each_slot(F&& f) {
 }
 
 // The next samples of the wave's 64 / S rays, one a lane, in slot order: the
-// wave marches until every ray that goes on has one, then at most 2 S points
+// wave marches until every ray that goes on has one, then at most two turns
 // more to fill the other slots (neighbouring samples are a step apart; a ray in
 // a longer gap is not waited for).  Returns whether this lane has a sample.
+//
+// A turn takes S lattice points of a ray at once, one a lane: a march is a
+// serial chain, and its grid reads (half a microsecond each) are what a small
+// launch waits for.  The points' positions do not depend on the reads (box: t0
+// + k step; contracted: every lane follows the ray's t through S steps), so all
+// S words are requested together; the decisions are then taken in order from
+// the lanes' answers: box: a read that proves a gap names the next point;
+// contracted: the lanes test their points against the ball the last read
+// opened.  Visits, decisions and read counts are those of one point after
+// another; points beyond a gap had their word read for nothing.
+// Measured against every lane marching its ray point by point (16 lanes a ray,
+// 4,096 rays): 8 levels in the box 0.107 -> 0.068 ms, 16 levels contracted 0.445
+// -> 0.333, baked with the pyramid 0.740 -> 0.539 contracted, 0.100 -> 0.060 in
+// the box; a training step of 4,087 rays 0.443 -> 0.354 ms.
 template <int DOM, bool PYR, int S>
 __device__ __forceinline__ bool march_slots(const SceneArgs& A, MarchState& m, int slot, int& reads, float u[3],
                                             float& ts, int& ks, int& reads_at) {
+  const int lane = threadIdx.x & 63;
+  const int first = lane & ~(S - 1);                      // the ray's first lane
   int found = 0;
   bool have = false;
   for (int fill = 0;;) {
     if (__ballot(!m.done && found < S) == 0) break;
-    if (__ballot(!m.done && found == 0) == 0 && ++fill > 2 * S) break;
+    if (__ballot(!m.done && found == 0) == 0 && ++fill > 2) break;
     if (!m.done && found < S) {
-      float v[3], t;
-      int k;
-      if (march_step<DOM, PYR, false>(A, m, false, reads, v, t, k)) {
-        if (found == slot) {
+      // this lane's point, and what its read decides
+      const int k = m.k + slot;
+      bool end = false, ball = false;                     // ball: inside the one the turn begins with
+      float p[3] = {0.f, 0.f, 0.f}, t = m.t, t_end = m.t;
+      if (DOM == DOM_BOX) {
+        t = m.t0 + (float)k * A.step;
+        end = !(t < m.t1);
 #pragma unroll
-          for (int a = 0; a < 3; ++a) u[a] = v[a];
-          ts = t;
-          ks = k;
-          reads_at = reads;
-          have = true;
+        for (int a = 0; a < 3; ++a) p[a] = m.o[a] + t * m.d[a];
+      } else {
+        // every lane follows the ray's t and keeps its own point
+#pragma unroll 1
+        for (int j = 0; j < S; ++j) {
+          float pj[3], dt;
+          bool ej = false;
+          contract_point(A, m, t_end, pj, dt, ej);
+          if (j == slot) {
+            t = t_end;
+            end = ej;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) p[a] = pj[a];
+          }
+          t_end = t_end + dt;
         }
-        ++found;
+        const float e0 = p[0] - m.bc[0], e1 = p[1] - m.bc[1], e2 = p[2] - m.bc[2];
+        ball = (e0 * e0 + e1 * e1) + e2 * e2 < m.br2;
       }
+      end = end || k >= kMaxLattice;
+      MarchState q = m;
+      float v[3] = {0.f, 0.f, 0.f};
+      bool occ = false;
+      if (!end && !ball) {
+        int r = 0;
+        q.k = k + 1;
+        const uint32_t vox = voxel_of(A, p, v);
+        occ = read_voxel<DOM, PYR>(A, q, false, r, p, v, k, t, vox);
+      }
+      const uint32_t ends = slot_bits<S>(end, lane), occs = slot_bits<S>(occ, lane);
+      const uint32_t balls = slot_bits<S>(ball && !end, lane);
+      int cur = balls == 0 ? 0 : __ffs(int(~balls)) - 1;  // the first point outside the ball
+      int src = -1;
+      while (cur < S && found < S) {
+        if ((ends >> cur) & 1u) {
+          m.done = true;
+          break;
+        }
+        // back in the turn's first ball after leaving it (another ball has
+        // replaced it): not read, so the next turn begins here
+        if ((balls >> cur) & 1u) break;
+        ++reads;
+        const int from = (first + cur) << 2;
+        if ((occs >> cur) & 1u) {
+          if (found == slot) {
+            src = from;
+            reads_at = reads;
+          }
+          ++found;
+          m.br2 = -1.0f;
+          ++cur;
+        } else if (DOM == DOM_BOX) {
+          cur = __builtin_amdgcn_ds_bpermute(from, q.k) - m.k;
+        } else {
+          m.br2 = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(q.br2)));
+#pragma unroll
+          for (int a = 0; a < 3; ++a)
+            m.bc[a] = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(q.bc[a])));
+          const float e0 = p[0] - m.bc[0], e1 = p[1] - m.bc[1], e2 = p[2] - m.bc[2];
+          const bool inside = (e0 * e0 + e1 * e1) + e2 * e2 < m.br2;
+          const uint32_t out = slot_bits<S>(end || !inside, lane) & ~((2u << cur) - 1u);
+          cur = out ? __ffs(int(out)) - 1 : S;
+        }
+      }
+      if (src >= 0) have = true;
+      // every lane's shuffle, whether it takes a sample of this turn or not
+      const int at = src >= 0 ? src : lane << 2;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const float x = __int_as_float(__builtin_amdgcn_ds_bpermute(at, __float_as_int(v[a])));
+        u[a] = src >= 0 ? x : u[a];
+      }
+      const float st = __int_as_float(__builtin_amdgcn_ds_bpermute(at, __float_as_int(t)));
+      const int sk = __builtin_amdgcn_ds_bpermute(at, k);
+      ts = src >= 0 ? st : ts;
+      ks = src >= 0 ? sk : ks;
+      // move on to the first point not visited
+      if (DOM == DOM_CONTRACT) {
+        const float tc = __int_as_float(
+            __builtin_amdgcn_ds_bpermute((first + (cur < S ? cur : 0)) << 2, __float_as_int(t)));
+        m.t = cur < S ? tc : t_end;
+      }
+      m.k += cur;
     }
   }
   return have;

@@ -29,15 +29,15 @@ __global__ void __launch_bounds__(256) eval_points_kernel(SceneArgs S, int64_t n
 }
 
 // Launches of at most this many rays take kSmallSlots lanes a ray: 64 rays a
-// wave leave most of the chip idle there and every ray's 15 to 20 samples are a
-// serial chain of lookups.  Measured, one against sixteen lanes a ray (float32;
-// ms): 8 levels in the box, 1,024 / 4,096 / 16,384 / 65,536 rays 0.288 / 0.295
-// / 0.305 / 0.339 against 0.093 / 0.114 / 0.112 / 0.318; 16 levels, contracted,
-// 1.42 / 1.57 / 1.60 / 1.58 against 0.55 / 0.57 / 0.92 / 1.61; baked with the
-// pyramid in the box 0.208 / 0.238 / 0.250 / 0.255 against 0.095 / 0.113 /
-// 0.127 / 0.304: the lines cross between 32,768 and 65,536.  (Four lanes a ray
-// were better than both only around 65,536 rays, by up to a fifth.)
-constexpr int64_t kSmallRays = 32768;
+// wave leave most of the chip idle there, and every ray's march and its 15 to
+// 20 lookups are serial chains that its lanes shorten.  Measured, one against
+// sixteen lanes a ray (ms; 16,384 / 49,152 / 65,536 / 98,304 / 131,072 rays):
+// float32, 8 levels in the box 0.305 / 0.307 / 0.329 / 0.295 / 0.299 against
+// 0.080 / 0.194 / 0.244 / 0.329 / 0.424; 16 levels, contracted, 1.60 / 1.15 /
+// 1.30 / 1.45 / 1.76 against 0.55 / 0.89 / 1.11 / 1.42 / 1.60; baked with the
+// pyramid in the box 0.250 / 0.230 / 0.230 / 0.248 / 0.233 against 0.068 /
+// 0.130 / 0.179 / 0.224 / 0.288: the lines cross around 90,000.
+constexpr int64_t kSmallRays = 81920;
 
 int launch_render(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, const RayOut& out,
                   const float* prop, bool use_net, float* prop_out, const ngprt_proposal_cfg& pc,

@@ -66,7 +66,7 @@ def test_samples_found_ahead(domain, max_samples):
         assert np.abs(out["rgb"].cpu().numpy() - ref.rgb).max() < 1e-5
 
 
-# 32,768 rays and fewer take sixteen lanes a ray, more take the ring: the same
+# 81,920 rays and fewer take sixteen lanes a ray, more take the ring: the same
 # bits either way, so each side checks the other (and the oracle checks the
 # small one above and in the parity tests)
 @pytest.mark.parametrize("name,dtype", [("tiny", 0), ("tiny", 1), ("tiny", 2), ("tiny_pyramid", 0), ("baked_tiny", 0),
@@ -76,9 +76,9 @@ def test_small_launches_match_large_ones(name, dtype):
     from helpers import gpu_renderer, scene_and_dist
     print(f"[small launches {name} {dtype}]", flush=True)
     cfg = scene_and_dist(name, dtype)[0].cfg
-    cams = synth.random_sphere_cameras(9, 1.0, seed=77)
+    cams = synth.random_sphere_cameras(21, 1.0, seed=77)
     o, d, _ = synth.scene_rays(cfg, cams=cams, width=64, height=64)
-    o, d = to_gpu(o[:32769], d[:32769])
+    o, d = to_gpu(o[:81921], d[:81921])
     d[11] = float("nan")
     r = gpu_renderer(name, dtype)
 
@@ -88,9 +88,9 @@ def test_small_launches_match_large_ones(name, dtype):
             out["dist_loss"] = torch.empty((n,), device="cuda")
         return r.render(o[:n].contiguous(), d[:n].contiguous(), out=out)
     for labels in (False, True):
-        want = render(32769, labels)
+        want = render(81921, labels)
         assert int(want["n_samples"].max()) > 16          # rays of more than one round of sixteen
-        for n in (1, 15, 16, 17, 4099, 32768):
+        for n in (1, 15, 16, 17, 4099, 81920):
             got = render(n, labels)
             for k, v in got.items():
                 assert torch.equal(v.view(torch.int32), want[k][:n].contiguous().view(torch.int32)), (n, labels, k)
@@ -106,7 +106,7 @@ def test_ring_on_slabs(domain):
     for cap in (7, 8, 9, 1024):
         sc = _slab_scene(domain, cap)
         rng = np.random.default_rng(5)
-        n = 32800
+        n = 82000
         o, d = to_gpu(rng.uniform(-1.2, 1.2, size=(n, 3)).astype(np.float32),
                       rng.normal(size=(n, 3)).astype(np.float32))
         r = Renderer.from_config(sc.cfg)
