@@ -16,7 +16,7 @@ enum { DOM_BOX = 0, DOM_CONTRACT = 1 };
 constexpr int kMaxLevels = NGPRT_MAX_LEVELS;
 constexpr int kMlpParams = 451;          // deferred MLP 7 -> 16 -> 16 -> 3
 constexpr int kMlpViewParams = 5891;     // view-dependent MLP 23 -> 64 -> 64 -> 3
-constexpr int kMlpViewRec = 8960;        // its weights arranged for the MFMA sequence
+constexpr int kMlpViewRec = 14336;       // its weights arranged for the MFMA sequence
 constexpr int kMaxLattice = 1 << 16;   // hard bound on lattice points per ray
 constexpr int kMaxPyr = 5;             // occupancy pyramid levels
 
@@ -111,7 +111,7 @@ struct ngprt_ctx {
   float scales_host[NGPRT_MAX_LEVELS][9];
   uint16_t* grid = nullptr;   // [R^3]
   float* mlp = nullptr;       // [451] or, view-dependent MLP, [5891]
-  float* mlp_rec = nullptr;   // view-dependent MLP: weights in MFMA order [8960]
+  float* mlp_rec = nullptr;   // view-dependent MLP: weights in MFMA order [kMlpViewRec]
   void* ws = nullptr;         // workspace (per-wave gradient partials of backward / proposal)
   size_t ws_bytes = 0;
   void* prop_wb = nullptr;    // proposal training: the weights as bfloat16 operand tiles [52][64] uint2
@@ -120,6 +120,7 @@ struct ngprt_ctx {
   bool prop_loaded = false;
   void* count_ws = nullptr;   // step auto-tuning: per-block partial sums of sample counts + total
   int vmlp_resident = 0;      // view_mlp_kernel workgroups resident together (0: not yet queried)
+  int vmlp_bwd_resident = 0;  // the same of view_mlp_backward_kernel
   bool det_grad = false;      // table gradients by sorted segment sums instead of atomics
   int32_t* cidx = nullptr;    // baked model: block index grid [nb^3]
   float* catlas = nullptr;    // baked model: atlas [n_blocks][512][Cpad]
