@@ -507,6 +507,8 @@ def kernel_source_hash() -> str:
 
 VALU_PEAK_G = 256 * 4 * 2.4 / 4     # wave64 VALU instructions per ns: 256 CUs x 4 SIMDs x 2.4 GHz,
                                    # one wave64 instruction per 4 cycles on a 16-lane SIMD
+                                   # (nominal: the BF16 render measures 1.15 of it, so some
+                                   # instructions issue faster)
 
 
 def committed_counters(dtype_name: str, scene: str = "hd"):

@@ -440,6 +440,7 @@ static int resident_groups(ngprt_ctx* ctx, Kernel kernel, int threads, int* out)
 
 int launch_view_mlp_backward(ngprt_ctx* ctx, int64_t n, const float* d, const float* c_d, const float* feat,
                              const float* grad_rgb, float* grad_cf, float* gmlp, hipStream_t st) {
+  if ((n + 63) / 64 > 0x7FFFFFFF) return fail(ctx, NGPRT_E_SHAPE, "too many rays for one launch");
   int rc = resident_groups(ctx, view_mlp_backward_kernel, 64 * kViewBwdWaves, &ctx->vmlp_bwd_resident);
   if (rc) return rc;
   const int64_t groups = (n + 16 * kViewBwdWaves - 1) / (16 * kViewBwdWaves);
