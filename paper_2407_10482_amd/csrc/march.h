@@ -269,7 +269,7 @@ template <int DOM, bool PYR, bool LO = false>
 __device__ __forceinline__ bool march_step(const SceneArgs& S, MarchState& m, bool naive,
                                            int& reads, float u[3], float& ts, int& ks) {
   const int kcur = m.k;
-  float p[3], tcur;
+  float p[3], tcur, dt = 0.0f;
   bool end = kcur >= kMaxLattice, need = true;
   if (DOM == DOM_BOX) {
     tcur = m.t0 + (float)kcur * S.step;
@@ -278,14 +278,13 @@ __device__ __forceinline__ bool march_step(const SceneArgs& S, MarchState& m, bo
     for (int a = 0; a < 3; ++a) p[a] = m.o[a] + tcur * m.d[a];
   } else {
     tcur = m.t;
-    float dt;
     contract_point(S, m, tcur, p, dt, end);
-    m.t = tcur + dt;
     // points in the known-empty ball take no read
     const float e0 = p[0] - m.bc[0], e1 = p[1] - m.bc[1], e2 = p[2] - m.bc[2];
     need = !((e0 * e0 + e1 * e1) + e2 * e2 < m.br2);
     if (LO) need = need && !(tcur < m.t_lo);
   }
+  // a stop at t_hi leaves the march at this point: a resumed ray visits it
   if (LO && !end && tcur > m.t_hi) {
     m.done = true;
     m.stopped_at_hi = true;
@@ -293,6 +292,7 @@ __device__ __forceinline__ bool march_step(const SceneArgs& S, MarchState& m, bo
   }
   m.done = end;
   m.k = kcur + 1;
+  if (DOM == DOM_CONTRACT) m.t = tcur + dt;
   if (end || !need) return false;
   ts = tcur;
   ks = kcur;
