@@ -339,7 +339,9 @@ int ngprt_debug_march(ngprt_ctx* ctx, int64_t n_rays, const float* dev_origins,
  * table gradients are summed with float atomics, so their low bits depend
  * on execution order (ngprt_set_deterministic_gradients removes that).  Needs float32 tables (NGPRT_E_DTYPE otherwise) and
  * the hash feature model (NGPRT_E_UNSUPPORTED for NGPRT_MODEL_BAKED).  May
- * grow a library-owned workspace (stream-ordered allocation). */
+ * grow a library-owned workspace and, for batches they speed up, padded
+ * gradient rows (stream-ordered allocations, kept by the context); without
+ * memory for the rows the call does without them. */
 int ngprt_render_backward(ngprt_ctx* ctx, int64_t n_rays, const float* dev_origins,
                           const float* dev_dirs, const float* dev_grad_rgb, float* dev_grad_tables,
                           float* dev_grad_mlp, void* stream);
@@ -388,7 +390,8 @@ int ngprt_set_deterministic_gradients(ngprt_ctx* ctx, int on);
  * thread), the next one fails as if the device were out of memory, and the
  * hook disarms; after < 0 disarms it.  The call that meets the failure
  * returns NGPRT_E_ALLOC (ngprt_create: and no context) and leaves its
- * context usable.  Always NGPRT_OK. */
+ * context usable; a backward that fails to get its padded rows goes on
+ * without them.  Always NGPRT_OK. */
 int ngprt_test_fail_alloc(int64_t after);
 
 /* For callers that cannot allocate device memory (code under stream

@@ -208,6 +208,7 @@ void ngprt_destroy(ngprt_ctx* ctx) {
   if (ctx->grid) (void)hipFree(ctx->grid);
   if (ctx->mlp) (void)hipFree(ctx->mlp);
   if (ctx->ws) (void)hipFree(ctx->ws);
+  if (ctx->pad_rows) (void)hipFree(ctx->pad_rows);
   if (ctx->prop_wb) (void)hipFree(ctx->prop_wb);
   if (ctx->prop_net) (void)hipFree(ctx->prop_net);
   if (ctx->prop_tmp) (void)hipFree(ctx->prop_tmp);

@@ -743,8 +743,8 @@ static bool is_baked_model(const ngprt_ctx* ctx) { return ctx->desc.feature_mode
 // Padded gradient rows.  The memory side takes float atomics by 64-byte
 // requests: a 36-byte row on its 36-byte stride costs 1.5 of them on average,
 // a row on a 64-byte line of its own costs one (13.9 and 20.9 G rows a
-// second).  So the scatter goes to rows of 16 floats in the workspace, which
-// are then added to the caller's.
+// second).  So the scatter goes to rows of 16 floats of the context's, which are
+// then added to the caller's.
 constexpr int kPadRow = 16;
 constexpr size_t kPadMaxBytes = size_t(1) << 30;
 
@@ -780,19 +780,32 @@ static int launch_add_rows(ngprt_ctx* ctx, const float* src, float* dst, int64_t
   return check_launch(ctx, "add_rows_kernel");
 }
 
+// The context's padded rows, grown to `bytes`; NULL when they cannot be had.
+// They are kept apart from the workspace: a backward needs the workspace, the
+// padded rows only make its scatter faster, so a device too full for them still
+// trains (on the caller's rows).
+static float* padded_rows(ngprt_ctx* ctx, size_t bytes, hipStream_t st) {
+  if (bytes > ctx->pad_bytes) {
+    if (ctx->pad_rows) (void)hipFreeAsync(ctx->pad_rows, st);
+    ctx->pad_rows = nullptr;
+    ctx->pad_bytes = 0;
+    if (dev_malloc_async((void**)&ctx->pad_rows, bytes, st) != hipSuccess) {
+      (void)hipGetLastError();
+      ctx->pad_rows = nullptr;
+      return nullptr;
+    }
+    ctx->pad_bytes = bytes;
+  }
+  return reinterpret_cast<float*>(ctx->pad_rows);
+}
+
 int launch_backward(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, const float* grad_rgb,
                     const float* grad_dist, const float* ups, const float* fcd, const float* ffv,
                     float* gtab, float* gatlas, float* gmlp, hipStream_t st) {
   if (backward_blocks(n) > 0x7FFFFFFF) return fail(ctx, NGPRT_E_SHAPE, "too many rays for one launch");
   const ngprt_desc& ds = ctx->desc;
   const bool baked = is_baked_model(ctx);
-  const size_t base = (backward_workspace_bytes(n) + 255) / 256 * 256;
-  const int64_t trows = int64_t(ds.n_levels) * ctx->T, arows = baked ? ctx->n_blocks * 512 : 0;
-  const bool tpad = !ctx->det_grad && pad_pays(n, ctx->T, trows);
-  const bool apad = !ctx->det_grad && arows > 0 && pad_pays(n, arows, arows);
-  const size_t tbytes = tpad ? size_t(trows) * kPadRow * sizeof(float) : 0;
-  const size_t abytes = apad ? size_t(arows) * kPadRow * sizeof(float) : 0;
-  const size_t need = base + tbytes + abytes;
+  const size_t need = backward_workspace_bytes(n);
   if (need > ctx->ws_bytes) {
     if (ctx->ws) (void)hipFreeAsync(ctx->ws, st);
     ctx->ws = nullptr;
@@ -808,12 +821,17 @@ int launch_backward(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, c
     if (baked) return fail(ctx, NGPRT_E_UNSUPPORTED, "deterministic gradients are built for the hash model");
     return launch_backward_det(ctx, n, o, d, grad_rgb, grad_dist, ups, fcd, ffv, gtab, gmlp, partial, st);
   }
-  float* tws = tpad ? reinterpret_cast<float*>(reinterpret_cast<char*>(ctx->ws) + base) : nullptr;
-  float* aws = apad ? reinterpret_cast<float*>(reinterpret_cast<char*>(ctx->ws) + base + tbytes) : nullptr;
-  if (tbytes + abytes > 0) {
-    const int64_t n4 = int64_t((tbytes + abytes) / sizeof(float4));
+  const int64_t trows = int64_t(ds.n_levels) * ctx->T, arows = baked ? ctx->n_blocks * 512 : 0;
+  bool tpad = pad_pays(n, ctx->T, trows), apad = arows > 0 && pad_pays(n, arows, arows);
+  const size_t tfloats = tpad ? size_t(trows) * kPadRow : 0, afloats = apad ? size_t(arows) * kPadRow : 0;
+  float* rows = tpad || apad ? padded_rows(ctx, (tfloats + afloats) * sizeof(float), st) : nullptr;
+  if (!rows) tpad = apad = false;
+  float* tws = rows;                                      // the tables' rows, then the atlas's
+  float* aws = rows ? rows + tfloats : nullptr;
+  if (rows) {
+    const int64_t n4 = int64_t((tfloats + afloats) / 4);
     hipLaunchKernelGGL(clear_rows_kernel, dim3(unsigned((n4 + 255) / 256)), dim3(256), 0, st,
-                       reinterpret_cast<float4*>(tpad ? tws : aws), n4);
+                       reinterpret_cast<float4*>(rows), n4);
     int rc = check_launch(ctx, "clear_rows_kernel");
     if (rc) return rc;
   }

@@ -112,8 +112,10 @@ struct ngprt_ctx {
   uint16_t* grid = nullptr;   // [R^3]
   float* mlp = nullptr;       // [451] or, view-dependent MLP, [5891]
   float* mlp_rec = nullptr;   // view-dependent MLP: weights in MFMA order [kMlpViewRec]
-  void* ws = nullptr;         // workspace (per-wave gradient partials of backward / proposal)
+  void* ws = nullptr;         // workspace (per-workgroup gradient partials of backward / view MLP / proposal)
   size_t ws_bytes = 0;
+  void* pad_rows = nullptr;   // padded gradient rows of the backward (optional: see padded_rows)
+  size_t pad_bytes = 0;
   void* prop_wb = nullptr;    // proposal training: the weights as bfloat16 operand tiles [52][64] uint2
   void* prop_net = nullptr;   // loaded proposal network: A-operand tiles [32][64] uint2 + biases [132]
   void* prop_tmp = nullptr;   // the same layout for ngprt_proposal_infer's caller-owned weights
