@@ -340,8 +340,8 @@ int ngprt_debug_march(ngprt_ctx* ctx, int64_t n_rays, const float* dev_origins,
  * on execution order (ngprt_set_deterministic_gradients removes that).  Needs float32 tables (NGPRT_E_DTYPE otherwise) and
  * the hash feature model (NGPRT_E_UNSUPPORTED for NGPRT_MODEL_BAKED).  May
  * grow a library-owned workspace and, for batches they speed up, padded
- * gradient rows (stream-ordered allocations, kept by the context); without
- * memory for the rows the call does without them. */
+ * gradient rows of at most 1 GiB (stream-ordered allocations, kept by the
+ * context); without memory for the rows the call does without them. */
 int ngprt_render_backward(ngprt_ctx* ctx, int64_t n_rays, const float* dev_origins,
                           const float* dev_dirs, const float* dev_grad_rgb, float* dev_grad_tables,
                           float* dev_grad_mlp, void* stream);

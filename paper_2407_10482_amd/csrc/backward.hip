@@ -746,14 +746,15 @@ static bool is_baked_model(const ngprt_ctx* ctx) { return ctx->desc.feature_mode
 // second).  So the scatter goes to rows of 16 floats of the context's, which are
 // then added to the caller's.
 constexpr int kPadRow = 16;
-constexpr size_t kPadMaxBytes = size_t(1) << 30;
+constexpr size_t kPadMaxBytes = size_t(1) << 30;    // of the tables' and the atlas's rows together
 
 // Whether `rows` rows pay for it: a ray sends some 50 rows a level, so padding
 // saves about 1.1 ns a ray and level, and costs 200 bytes a row to clear, read
 // and add, 44 ps: it pays from about rows / 25 rays on (of a level's rows).  Measured
 // on the step of 2^18 rays, 16 x 2^19 tables: 16.7 -> 15.4 ms.
-static bool pad_pays(int64_t n, int64_t rows_per_level, int64_t rows) {
-  return n >= rows_per_level / 16 && size_t(rows) * kPadRow * sizeof(float) <= kPadMaxBytes;
+// limit: the bytes that the rows may take.
+static bool pad_pays(int64_t n, int64_t rows_per_level, int64_t rows, size_t limit) {
+  return n >= rows_per_level / 16 && size_t(rows) * kPadRow * sizeof(float) <= limit;
 }
 
 __global__ void clear_rows_kernel(float4* __restrict__ p, int64_t n) {
@@ -822,8 +823,11 @@ int launch_backward(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, c
     return launch_backward_det(ctx, n, o, d, grad_rgb, grad_dist, ups, fcd, ffv, gtab, gmlp, partial, st);
   }
   const int64_t trows = int64_t(ds.n_levels) * ctx->T, arows = baked ? ctx->n_blocks * 512 : 0;
-  bool tpad = pad_pays(n, ctx->T, trows), apad = arows > 0 && pad_pays(n, arows, arows);
-  const size_t tfloats = tpad ? size_t(trows) * kPadRow : 0, afloats = apad ? size_t(arows) * kPadRow : 0;
+  // the tables' rows first, the atlas's if they still fit
+  bool tpad = pad_pays(n, ctx->T, trows, kPadMaxBytes);
+  const size_t tfloats = tpad ? size_t(trows) * kPadRow : 0;
+  bool apad = arows > 0 && pad_pays(n, arows, arows, kPadMaxBytes - tfloats * sizeof(float));
+  const size_t afloats = apad ? size_t(arows) * kPadRow : 0;
   float* rows = tpad || apad ? padded_rows(ctx, (tfloats + afloats) * sizeof(float), st) : nullptr;
   if (!rows) tpad = apad = false;
   float* tws = rows;                                      // the tables' rows, then the atlas's

@@ -76,3 +76,31 @@ def test_no_memory_for_padded_rows(name, n):
     _lib().ngprt_test_fail_alloc(-1)
     got = _grads(r, o, d, g)
     assert all(_close(a, b) for a, b in zip(got, want))
+
+
+def test_padded_rows_hold_at_most_one_gib():
+    """A baked scene whose tables (4 x 2^22) and atlas (2^15 blocks) would each
+    take 1 GiB of padded rows."""
+    import torch
+    from paper_2407_10482_amd.renderer import Renderer
+    print("[padded rows: memory held]", flush=True)
+    blocks = 1 << 15
+    r = Renderer([256, 512, 1024, 2048], 22, occ_res=32, feature_model=1, coarse_res=255)
+    r.load_tables(torch.zeros((4, 1 << 22, 9), device="cuda"))
+    r.load_occupancy(torch.ones((32, 32, 32), dtype=torch.uint8, device="cuda"))
+    r.load_mlp(torch.zeros((451,), device="cuda"))
+    index = torch.arange(blocks, dtype=torch.int32, device="cuda").view(32, 32, 32)
+    r.load_coarse(index, torch.zeros((blocks, 8, 8, 8, 16), device="cuda"), [0.0] * 16)
+    n = 1 << 20
+    o, g = torch.zeros((n, 3), device="cuda"), torch.ones((n, 3), device="cuda")
+    d = torch.zeros((n, 3), device="cuda")                # rays without a direction: no samples
+    grads = [torch.zeros(s, device="cuda") for s in ((4, 1 << 22, 9), (blocks, 8, 8, 8, 16), (451,))]
+    r.backward_baked(o[:64], d[:64], g[:64], *grads)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    r.backward_baked(o, d, g, *grads)
+    torch.cuda.synchronize()
+    held = before - torch.cuda.mem_get_info()[0]
+    # the rows, 30 MB of partials, and the allocator's rounding
+    assert (1 << 30) <= held <= (1 << 30) + (128 << 20), held
+    assert float(grads[0].abs().max()) == 0.0 and float(grads[1].abs().max()) == 0.0
