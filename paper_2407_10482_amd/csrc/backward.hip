@@ -762,22 +762,24 @@ __global__ void clear_rows_kernel(float4* __restrict__ p, int64_t n) {
   if (i < n) p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// dst[r * C + c] += src[r * kPadRow + c] for the first nv of C channels
-__global__ void add_rows_kernel(const float* __restrict__ src, float* __restrict__ dst, int64_t rows, int C, int nv) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= rows * C) return;
-  const int64_t r = i / C;
-  const int c = int(i - r * C);
+// dst[r * C + c] += src[r * kPadRow + c] for the first nv of C channels, by
+// atomics like every other addition to a caller's rows: contexts on other
+// streams may be adding to the same gradient.
+// n = rows * C < 2^32 (kPadMaxBytes holds 2^24 rows of at most 16 channels).
+__global__ void add_rows_kernel(const float* __restrict__ src, float* __restrict__ dst, uint32_t n, uint32_t C,
+                                uint32_t nv) {
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const uint32_t r = i / C, c = i - r * C;
   if (c >= nv) return;
-  const float v = src[r * kPadRow + c];
-  if (v != 0.0f) dst[i] += v;
+  const float v = src[size_t(r) * kPadRow + c];
+  if (v != 0.0f) unsafeAtomicAdd(dst + i, v);
 }
 
 static int launch_add_rows(ngprt_ctx* ctx, const float* src, float* dst, int64_t rows, int C, int nv,
                            hipStream_t st) {
-  const int64_t blocks = (rows * C + 255) / 256;
-  if (blocks > 0x7FFFFFFF) return fail(ctx, NGPRT_E_SHAPE, "gradient too large for one launch");
-  hipLaunchKernelGGL(add_rows_kernel, dim3(unsigned(blocks)), dim3(256), 0, st, src, dst, rows, C, nv);
+  const uint32_t n = uint32_t(rows) * uint32_t(C);
+  hipLaunchKernelGGL(add_rows_kernel, dim3((n + 255) / 256), dim3(256), 0, st, src, dst, n, uint32_t(C), uint32_t(nv));
   return check_launch(ctx, "add_rows_kernel");
 }
 

@@ -104,3 +104,26 @@ def test_padded_rows_hold_at_most_one_gib():
     # the rows, 30 MB of partials, and the allocator's rounding
     assert (1 << 30) <= held <= (1 << 30) + (128 << 20), held
     assert float(grads[0].abs().max()) == 0.0 and float(grads[1].abs().max()) == 0.0
+
+
+def test_two_contexts_add_to_one_gradient():
+    """Contexts on two streams accumulate into one table gradient: every
+    addition to it is atomic, the padded rows' too."""
+    import torch
+    print("[padded rows: two contexts, one gradient]", flush=True)
+    n, times = 16500, 24
+    o, d, g = _rays("tiny", n)
+    cf = torch.cat([g, g[:, :1].expand(n, 4)], 1).contiguous()
+    rs = [gpu_renderer("tiny"), gpu_renderer("tiny")]
+    one = torch.zeros((rs[0].L, rs[0].T, 9), device="cuda")
+    rs[0].backward_features(o, d, cf, one)
+    both = torch.zeros_like(one)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for _ in range(times):
+        for r, s in zip(rs, streams):
+            with torch.cuda.stream(s):
+                r.backward_features(o, d, cf, both)
+    torch.cuda.synchronize()
+    # 48 additions to one float: their rounding is within the norm's tolerance
+    assert float(one.abs().max()) > 0 and _close(both, one * (2 * times))
