@@ -729,10 +729,16 @@ __global__ void adam_kernel(int64_t n, float* __restrict__ p, const float* __res
 // march_slots), 2^10 rays 2.29 / 1.24 / 0.83 / 0.67 / 0.64 ms.
 static int backward_slots(int64_t n) { return n <= 16384 ? 16 : 4; }
 
-static int64_t backward_blocks(int64_t n) {
+// workgroups of m rays of a batch of n
+static int64_t backward_blocks(int64_t m, int64_t n) {
   const int64_t rays = 256 / backward_slots(n);          // per workgroup
-  return (n + rays - 1) / rays;
+  return (m + rays - 1) / rays;
 }
+static int64_t backward_blocks(int64_t n) { return backward_blocks(n, n); }
+
+// Rays of one launch, a multiple of a workgroup's: a launch holds fewer than
+// 2^32 threads, and these are 2^31 at four lanes a ray.
+constexpr int64_t kLaunchRays = int64_t(1) << 29;
 
 size_t backward_workspace_bytes(int64_t n) {
   return (size_t(backward_blocks(n)) + kSumGroups) * kMlpParams * sizeof(float);
@@ -805,7 +811,7 @@ static float* padded_rows(ngprt_ctx* ctx, size_t bytes, hipStream_t st) {
 int launch_backward(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, const float* grad_rgb,
                     const float* grad_dist, const float* ups, const float* fcd, const float* ffv,
                     float* gtab, float* gatlas, float* gmlp, hipStream_t st) {
-  if (backward_blocks(n) > 0x7FFFFFFF) return fail(ctx, NGPRT_E_SHAPE, "too many rays for one launch");
+  if (backward_blocks(n) > 0x7FFFFFFF) return fail(ctx, NGPRT_E_SHAPE, "too many rays");
   const ngprt_desc& ds = ctx->desc;
   const bool baked = is_baked_model(ctx);
   const size_t need = backward_workspace_bytes(n);
@@ -855,13 +861,13 @@ int launch_backward_ws(ngprt_ctx* ctx, int64_t n, const float* o, const float* d
                        hipStream_t st, const DetRecords& det) {
   SceneArgs S = scene_args(ctx);
   const int64_t blocks = backward_blocks(n);
-  if (blocks > 0x7FFFFFFF) return fail(ctx, NGPRT_E_SHAPE, "too many rays for one launch");
-  dim3 g = dim3(unsigned(blocks));
+  if (blocks > 0x7FFFFFFF) return fail(ctx, NGPRT_E_SHAPE, "too many rays");
   const bool box = ctx->desc.domain == DOM_BOX;
   const bool wide = backward_slots(n) == 16;
 #define NGPRT_BW_S(DOMV, LM, PY, MD, SL)                                                               \
-  hipLaunchKernelGGL((backward_kernel<DOMV, LM, PY, MD, SL>), g, dim3(256), 0, st, S, n, o, d, grad_rgb, \
-                     grad_dist, ups, fcd, ffv, gtab, tstride, gatlas, astride, partial, ctx->mlp, det)
+  hipLaunchKernelGGL((backward_kernel<DOMV, LM, PY, MD, SL>), g, dim3(256), 0, st, S, m, o + 3 * at, d + 3 * at, \
+                     from(grad_rgb, 3), from(grad_dist, 1), from(ups, 7), from(fcd, 3), from(ffv, 4), gtab,    \
+                     tstride, gatlas, astride, part, ctx->mlp, rec)
 #define NGPRT_BW(DOMV, LM, PY, MD)          \
   if (wide) NGPRT_BW_S(DOMV, LM, PY, MD, 16); \
   else NGPRT_BW_S(DOMV, LM, PY, MD, 4)
@@ -871,23 +877,31 @@ int launch_backward_ws(ngprt_ctx* ctx, int64_t n, const float* o, const float* d
   } else {                               \
     NGPRT_BW(DOM_CONTRACT, LM, PY, MD);  \
   }
-  if (S.model == NGPRT_MODEL_BAKED) {
-    // L <= 2 fine levels: coarse rows of at most 12 channels
-    if (S.L <= 2 && S.pyr_n > 0) {
-      NGPRT_BW_DOM(2, true, 1)
-    } else if (S.L <= 2) {
-      NGPRT_BW_DOM(2, false, 1)
+  for (int64_t at = 0; at < n; at += kLaunchRays) {
+    const int64_t m = n - at < kLaunchRays ? n - at : kLaunchRays;
+    const dim3 g(unsigned(backward_blocks(m, n)));
+    auto from = [at](const float* p, int width) { return p ? p + width * at : nullptr; };
+    float* part = partial + backward_blocks(at, n) * kMlpParams;
+    DetRecords rec = det;
+    if (rec.off) rec.off += at;
+    if (S.model == NGPRT_MODEL_BAKED) {
+      // L <= 2 fine levels: coarse rows of at most 12 channels
+      if (S.L <= 2 && S.pyr_n > 0) {
+        NGPRT_BW_DOM(2, true, 1)
+      } else if (S.L <= 2) {
+        NGPRT_BW_DOM(2, false, 1)
+      } else if (S.pyr_n > 0) {
+        NGPRT_BW_DOM(4, true, 1)
+      } else {
+        NGPRT_BW_DOM(4, false, 1)
+      }
     } else if (S.pyr_n > 0) {
-      NGPRT_BW_DOM(4, true, 1)
+      NGPRT_BW_DOM(16, true, 0)
+    } else if (S.L <= 8) {
+      NGPRT_BW_DOM(8, false, 0)
     } else {
-      NGPRT_BW_DOM(4, false, 1)
+      NGPRT_BW_DOM(16, false, 0)
     }
-  } else if (S.pyr_n > 0) {
-    NGPRT_BW_DOM(16, true, 0)
-  } else if (S.L <= 8) {
-    NGPRT_BW_DOM(8, false, 0)
-  } else {
-    NGPRT_BW_DOM(16, false, 0)
   }
 #undef NGPRT_BW_DOM
 #undef NGPRT_BW

@@ -127,3 +127,22 @@ def test_two_contexts_add_to_one_gradient():
     torch.cuda.synchronize()
     # 48 additions to one float: their rounding is within the norm's tolerance
     assert float(one.abs().max()) > 0 and _close(both, one * (2 * times))
+
+
+def test_more_threads_than_a_launch_holds():
+    """2^30 rays and more (2^32 threads at four lanes a ray) go in several
+    launches: rays with samples around the parts' ends, the others empty."""
+    import torch
+    print("[backward of 2^30 rays]", flush=True)
+    if torch.cuda.mem_get_info()[0] < 90 << 30:
+        pytest.skip("needs 90 GiB of device memory")
+    o, d, g = _rays("tiny", 128)
+    want = _grads(gpu_renderer("tiny"), o, d, g)
+    n = (1 << 30) + 32
+    big = [torch.zeros((n, 3), device="cuda") for _ in range(3)]
+    for k, at in enumerate(((1 << 29) - 32, (1 << 30) - 32)):
+        for whole, x in zip(big, (o, d, g)):
+            whole[at:at + 64] = x[64 * k:64 * k + 64]
+    got = _grads(gpu_renderer("tiny"), *big)
+    torch.cuda.synchronize()
+    assert all(float(b.abs().max()) > 0 and _close(a, b) for a, b in zip(got, want))
