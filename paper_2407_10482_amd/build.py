@@ -19,7 +19,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libngprt.so")
 BUILD_DIR = os.path.join(HERE, "_build")
-SOURCES = ["api.hip", "render.hip", "render_plain.hip", "render_ext.hip", "render_march.hip", "render_small.hip", "grid.hip", "tables.hip", "backward.hip", "proposal.hip", "probe.hip", "mlp_view.hip", "noalloc.hip", "tuning.hip", "det.hip"]
+SOURCES = ["api.hip", "render.hip", "render_plain.hip", "render_ext.hip", "render_march.hip", "render_small.hip", "render_mid.hip", "grid.hip", "tables.hip", "backward.hip", "proposal.hip", "probe.hip", "mlp_view.hip", "noalloc.hip", "tuning.hip", "det.hip"]
 ARCH = "gfx950"
 
 FLAGS = [

@@ -28,16 +28,30 @@ __global__ void __launch_bounds__(256) eval_points_kernel(SceneArgs S, int64_t n
       for (int k = 0; k < 8; ++k) idx[(i * S.L + l) * 8 + k] = id[l * 8 + k];
 }
 
-// Launches of at most this many rays take kSmallSlots lanes a ray: 64 rays a
-// wave leave most of the chip idle there, and every ray's march and its 15 to
-// 20 lookups are serial chains that its lanes shorten.  Measured, one against
-// sixteen lanes a ray (ms; 16,384 / 49,152 / 65,536 / 98,304 / 131,072 rays):
-// float32, 8 levels in the box 0.305 / 0.307 / 0.329 / 0.295 / 0.299 against
-// 0.080 / 0.194 / 0.244 / 0.329 / 0.424; 16 levels, contracted, 1.60 / 1.15 /
-// 1.30 / 1.45 / 1.76 against 0.55 / 0.89 / 1.11 / 1.42 / 1.60; baked with the
-// pyramid in the box 0.250 / 0.230 / 0.230 / 0.248 / 0.233 against 0.068 /
-// 0.130 / 0.179 / 0.224 / 0.288: the lines cross around 90,000.
-constexpr int64_t kSmallRays = 81920;
+// Lanes a ray of a render without a proposal.  64 rays a wave leave most of the
+// chip idle in a small launch, and every ray's march and its 15 to 20 lookups are
+// serial chains that its lanes shorten; but lanes past a ray's last sample look
+// up for nothing, and each lane of a contracted march follows its ray through
+// all lanes' points, so the lanes cost more the fewer samples the rays take and
+// the fuller the chip is.  Measured, 1 / 8 / 16 lanes a ray (ms), scenes of 15 to
+// 17 samples a ray:
+//   rays                     16,384             32,768             49,152             65,536             81,760
+//   F32, 8 levels, box       .253 / .108 / .076 .265 / .128 / .129 .317 / .137 / .184 .325 / .179 / .239 .305 / .206 / .274
+//   baked, pyramid, box      .213 / .089 / .066 .209 / .097 / .099 .233 / .108 / .124 .230 / .153 / .170 .232 / .164 / .195
+//   F32, 16 levels, contr.   1.13 / .660 / .554 1.09 / .708 / .671 1.15 / .965 / .883 1.32 / 1.07 / 1.12 1.46 / 1.19 / 1.25
+//   baked, pyramid, contr.   1.50 / .799 / .546 1.76 / .907 / .588 1.80 / .933 / .788 1.87 / .893 / .959 1.94 / 1.06 / 1.09
+// and with one sample a ray (solid surfaces):
+//   F32, 8 levels, box       .057 / .052 / .050 .058 / .060 / .088 .058 / .071 / .114 .058 / .088 / .154 .064 / .093 / .173
+//   F32, 16 levels, contr.   .420 / .335 / .372 .415 / .396 / .501 .423 / .515 / .723 .410 / .587 / .921 .441 / .652 / 1.04
+// Sixteen to where eight are no slower on the first, eight to where one lane is
+// as good.  (Contracted rays that meet nothing at all pay most, .26 / .58 / 1.00 at
+// 49,152; any share of rays that do sample hides it: one lane a ray is then bound
+// by its longest rays.)  A ray cut off after three samples has no use for the
+// lanes.
+static int render_lanes(const SceneArgs& S, int domain, int64_t n) {
+  if (S.max_samples < 4 || n > 81920) return 1;
+  return n <= (domain == DOM_BOX ? 28672 : 61440) ? kSmallSlots : kMidSlots;
+}
 
 int launch_render(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, const RayOut& out,
                   const float* prop, bool use_net, float* prop_out, const ngprt_proposal_cfg& pc,
@@ -53,7 +67,9 @@ int launch_render(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, con
                   pc.conf_threshold, pc.margin, pc.use_near, pc.far_guard, fallback};
   const bool ext = prop || use_net || out.t_first || out.t_far || out.t_half || out.dist_loss;
 #define NGPRT_FAMILY(f) f(S, ctx->desc.domain, ctx->desc.table_dtype, st, n, o, d, out, rec, ctx->mlp, 0, pa)
-  if (!prop && !use_net && n <= kSmallRays) NGPRT_FAMILY(render_small);
+  const int lanes = prop || use_net ? 1 : render_lanes(S, ctx->desc.domain, n);
+  if (lanes == kSmallSlots) NGPRT_FAMILY(render_small);
+  else if (lanes == kMidSlots) NGPRT_FAMILY(render_mid);
   else if (ext) NGPRT_FAMILY(render_ext);
   else NGPRT_FAMILY(render_plain);
 #undef NGPRT_FAMILY

@@ -440,8 +440,10 @@ static inline void dispatch(const SceneArgs& S, int dom, int dt, hipStream_t st,
 void render_plain(NGPRT_DISPATCH_ARGS);     // MODE_RENDER
 void render_ext(NGPRT_DISPATCH_ARGS);       // MODE_RENDER_EXT
 void render_march(NGPRT_DISPATCH_ARGS);     // MODE_MARCH
-void render_small(NGPRT_DISPATCH_ARGS);     // kSmallSlots lanes a ray, with or without the label outputs
+// several lanes a ray, with or without the label outputs
+void render_small(NGPRT_DISPATCH_ARGS);     // kSmallSlots
+void render_mid(NGPRT_DISPATCH_ARGS);       // kMidSlots
 
-constexpr int kSmallSlots = 16;
+constexpr int kSmallSlots = 16, kMidSlots = 8;
 
 }  // namespace ngprt
