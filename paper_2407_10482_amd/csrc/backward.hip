@@ -274,11 +274,11 @@ __device__ __forceinline__ bf32x4 wave_outer_sum(const float* sA, const float* s
 // Vertices of empty blocks take the default vector and receive no gradient.
 // Every lane of the wave takes part (have = false: no contribution).
 // gtab: [L][T][tstride] (channel 8, the hash model's logit, untouched); gatlas:
-// [n_blocks][8][8][8][astride], of which C = 8 + 2 L.
+// [n_blocks][8][8][8][C], C = 8 + 2 L.
 template <int LMAX>
 __device__ __forceinline__ void baked_scatter(const SceneArgs& S, const float u[3], bool have, const float gf[8],
                                               float w, const GradSink<LMAX>& q, float* __restrict__ gtab,
-                                              int tstride, float* __restrict__ gatlas, int astride, int lane,
+                                              int tstride, float* __restrict__ gatlas, int lane,
                                               float* stage) {
   static_assert(LMAX <= 4, "the coarse row holds at most 16 channels");
   constexpr int CMAX = 8 + 2 * LMAX;
@@ -333,7 +333,7 @@ __device__ __forceinline__ void baked_scatter(const SceneArgs& S, const float u[
   }
   // the cell's coordinates, below 2^11 each
   const uint32_t key = uint32_t(i0[0]) | (uint32_t(i0[1]) << 11);
-  scatter_cells<CMAX>(gatlas, astride, C, have, key, uint32_t(i0[2]), idx, wk, gco, lane, stage);
+  scatter_cells<CMAX>(gatlas, C, C, have, key, uint32_t(i0[2]), idx, wk, gco, lane, stage);
 }
 
 // SLOTS: lanes a ray (see march_slots); a workgroup holds 256 / SLOTS rays and
@@ -347,7 +347,7 @@ __global__ void __launch_bounds__(256) backward_kernel(SceneArgs S, int64_t n, c
                                                        const float* __restrict__ fcd,
                                                        const float* __restrict__ ffv,
                                                        float* __restrict__ gtab, int tstride,
-                                                       float* __restrict__ gatlas, int astride,
+                                                       float* __restrict__ gatlas,
                                                        float* __restrict__ partial,
                                                        const float* __restrict__ P, DetRecords det) {
   __shared__ __align__(16) float stage_all[4][kStageFloats];
@@ -665,7 +665,7 @@ __global__ void __launch_bounds__(256) backward_kernel(SceneArgs S, int64_t n, c
       for (int j = 0; j < 4; ++j) gf[4 + j] = w * gfv[j];
     }
     if constexpr (MODEL == 1) {
-      baked_scatter<LMAX>(S, u, have, gf, w, q, gtab, tstride, gatlas, astride, lane, stage);
+      baked_scatter<LMAX>(S, u, have, gf, w, q, gtab, tstride, gatlas, lane, stage);
       continue;
     }
 #pragma unroll 1
@@ -746,21 +746,21 @@ size_t backward_workspace_bytes(int64_t n) {
 
 static bool is_baked_model(const ngprt_ctx* ctx) { return ctx->desc.feature_model == NGPRT_MODEL_BAKED; }
 
-// Padded gradient rows.  The memory side takes float atomics by 64-byte
-// requests: a 36-byte row on its 36-byte stride costs 1.5 of them on average,
-// a row on a 64-byte line of its own costs one (13.9 and 20.9 G rows a
+// Padded gradient rows of the tables.  The memory side takes float atomics by
+// 64-byte requests: a 36-byte row on its 36-byte stride costs 1.5 of them on
+// average, a row on a 64-byte line of its own costs one (13.9 and 20.9 G rows a
 // second).  So the scatter goes to rows of 16 floats of the context's, which are
-// then added to the caller's.
+// then added to the caller's.  (The baked model's atlas rows of 10 to 16 floats
+// gain nothing by it: 2^18 rays on 124,416 to 1.6 M atlas rows, 1.74 to 1.81 ms
+// without, 1.78 to 1.84 with.)
 constexpr int kPadRow = 16;
-constexpr size_t kPadMaxBytes = size_t(1) << 30;    // of the tables' and the atlas's rows together
+constexpr size_t kPadMaxBytes = size_t(1) << 30;
 
-// Whether `rows` rows pay for it: a ray sends some 50 rows a level, so padding
-// saves about 1.1 ns a ray and level, and costs 200 bytes a row to clear, read
-// and add, 44 ps: it pays from about rows / 25 rays on (of a level's rows).  Measured
+// Whether `rows` rows pay for it: they cost 200 bytes a row to clear, read and
+// add, 44 ps, and save the less the fewer rows a batch sends.  Measured
 // on the step of 2^18 rays, 16 x 2^19 tables: 16.7 -> 15.4 ms.
-// limit: the bytes that the rows may take.
-static bool pad_pays(int64_t n, int64_t rows_per_level, int64_t rows, size_t limit) {
-  return n >= rows_per_level / 16 && size_t(rows) * kPadRow * sizeof(float) <= limit;
+static bool pad_pays(int64_t n, int64_t rows_per_level, int64_t rows) {
+  return n >= rows_per_level / 16 && size_t(rows) * kPadRow * sizeof(float) <= kPadMaxBytes;
 }
 
 __global__ void clear_rows_kernel(float4* __restrict__ p, int64_t n) {
@@ -768,24 +768,22 @@ __global__ void clear_rows_kernel(float4* __restrict__ p, int64_t n) {
   if (i < n) p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// dst[r * C + c] += src[r * kPadRow + c] for the first nv of C channels, by
+// dst[9 r + c] += src[r * kPadRow + c] for the first nv of a row's 9 channels, by
 // atomics like every other addition to a caller's rows: contexts on other
-// streams may be adding to the same gradient.
-// n = rows * C < 2^32 (kPadMaxBytes holds 2^24 rows of at most 16 channels).
-__global__ void add_rows_kernel(const float* __restrict__ src, float* __restrict__ dst, uint32_t n, uint32_t C,
-                                uint32_t nv) {
+// streams may be adding to the same gradient.  n = 9 rows < 2^32 (kPadMaxBytes
+// holds 2^24 rows).
+__global__ void add_rows_kernel(const float* __restrict__ src, float* __restrict__ dst, uint32_t n, uint32_t nv) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const uint32_t r = i / C, c = i - r * C;
+  const uint32_t r = i / 9, c = i - r * 9;
   if (c >= nv) return;
   const float v = src[size_t(r) * kPadRow + c];
   if (v != 0.0f) unsafeAtomicAdd(dst + i, v);
 }
 
-static int launch_add_rows(ngprt_ctx* ctx, const float* src, float* dst, int64_t rows, int C, int nv,
-                           hipStream_t st) {
-  const uint32_t n = uint32_t(rows) * uint32_t(C);
-  hipLaunchKernelGGL(add_rows_kernel, dim3((n + 255) / 256), dim3(256), 0, st, src, dst, n, uint32_t(C), uint32_t(nv));
+static int launch_add_rows(ngprt_ctx* ctx, const float* src, float* dst, int64_t rows, int nv, hipStream_t st) {
+  const uint32_t n = uint32_t(rows) * 9u;
+  hipLaunchKernelGGL(add_rows_kernel, dim3((n + 255) / 256), dim3(256), 0, st, src, dst, n, uint32_t(nv));
   return check_launch(ctx, "add_rows_kernel");
 }
 
@@ -818,7 +816,6 @@ int launch_backward(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, c
                     const float* grad_dist, const float* ups, const float* fcd, const float* ffv,
                     float* gtab, float* gatlas, float* gmlp, hipStream_t st) {
   if (backward_blocks(n) > 0x7FFFFFFF) return fail(ctx, NGPRT_E_SHAPE, "too many rays");
-  const ngprt_desc& ds = ctx->desc;
   const bool baked = is_baked_model(ctx);
   const size_t need = backward_workspace_bytes(n);
   if (need > ctx->ws_bytes) {
@@ -836,34 +833,25 @@ int launch_backward(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, c
     if (baked) return fail(ctx, NGPRT_E_UNSUPPORTED, "deterministic gradients are built for the hash model");
     return launch_backward_det(ctx, n, o, d, grad_rgb, grad_dist, ups, fcd, ffv, gtab, gmlp, partial, st);
   }
-  const int64_t trows = int64_t(ds.n_levels) * ctx->T, arows = baked ? ctx->n_blocks * 512 : 0;
-  // the tables' rows first, the atlas's if they still fit
-  bool tpad = pad_pays(n, ctx->T, trows, kPadMaxBytes);
-  const size_t tfloats = tpad ? size_t(trows) * kPadRow : 0;
-  bool apad = arows > 0 && pad_pays(n, arows, arows, kPadMaxBytes - tfloats * sizeof(float));
-  const size_t afloats = apad ? size_t(arows) * kPadRow : 0;
-  float* rows = tpad || apad ? padded_rows(ctx, (tfloats + afloats) * sizeof(float), st) : nullptr;
-  if (!rows) tpad = apad = false;
-  float* tws = rows;                                      // the tables' rows, then the atlas's
-  float* aws = rows ? rows + tfloats : nullptr;
+  const int64_t trows = int64_t(ctx->desc.n_levels) * ctx->T;
+  const size_t floats = size_t(trows) * kPadRow;
+  float* rows = pad_pays(n, ctx->T, trows) ? padded_rows(ctx, floats * sizeof(float), st) : nullptr;
   if (rows) {
-    const int64_t n4 = int64_t((tfloats + afloats) / 4);
+    const int64_t n4 = int64_t(floats / 4);
     hipLaunchKernelGGL(clear_rows_kernel, dim3(unsigned((n4 + 255) / 256)), dim3(256), 0, st,
                        reinterpret_cast<float4*>(rows), n4);
     int rc = check_launch(ctx, "clear_rows_kernel");
     if (rc) return rc;
   }
-  const int C = 8 + 2 * ds.n_levels;                      // atlas channels of the baked model
-  int rc = launch_backward_ws(ctx, n, o, d, grad_rgb, grad_dist, ups, fcd, ffv, tpad ? tws : gtab,
-                              tpad ? kPadRow : 9, apad ? aws : gatlas, apad ? kPadRow : C, gmlp, partial, st);
-  if (rc == NGPRT_OK && tpad) rc = launch_add_rows(ctx, tws, gtab, trows, 9, baked ? 8 : 9, st);
-  if (rc == NGPRT_OK && apad) rc = launch_add_rows(ctx, aws, gatlas, arows, C, C, st);
+  int rc = launch_backward_ws(ctx, n, o, d, grad_rgb, grad_dist, ups, fcd, ffv, rows ? rows : gtab, rows ? kPadRow : 9,
+                              gatlas, gmlp, partial, st);
+  if (rc == NGPRT_OK && rows) rc = launch_add_rows(ctx, rows, gtab, trows, baked ? 8 : 9, st);
   return rc;
 }
 
 int launch_backward_ws(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, const float* grad_rgb,
                        const float* grad_dist, const float* ups, const float* fcd, const float* ffv,
-                       float* gtab, int tstride, float* gatlas, int astride, float* gmlp, float* partial,
+                       float* gtab, int tstride, float* gatlas, float* gmlp, float* partial,
                        hipStream_t st, const DetRecords& det) {
   SceneArgs S = scene_args(ctx);
   const int64_t blocks = backward_blocks(n);
@@ -873,7 +861,7 @@ int launch_backward_ws(ngprt_ctx* ctx, int64_t n, const float* o, const float* d
 #define NGPRT_BW_S(DOMV, LM, PY, MD, SL)                                                               \
   hipLaunchKernelGGL((backward_kernel<DOMV, LM, PY, MD, SL>), g, dim3(256), 0, st, S, m, o + 3 * at, d + 3 * at, \
                      from(grad_rgb, 3), from(grad_dist, 1), from(ups, 7), from(fcd, 3), from(ffv, 4), gtab,    \
-                     tstride, gatlas, astride, part, ctx->mlp, rec)
+                     tstride, gatlas, part, ctx->mlp, rec)
 #define NGPRT_BW(DOMV, LM, PY, MD)          \
   if (wide) NGPRT_BW_S(DOMV, LM, PY, MD, 16); \
   else NGPRT_BW_S(DOMV, LM, PY, MD, 4)

@@ -90,7 +90,7 @@ int launch_backward_det(ngprt_ctx* ctx, int64_t n, const float* o, const float* 
   if (rc == NGPRT_OK) {
     det.off = off_dev;
     det.n = n_rec;
-    rc = launch_backward_ws(ctx, n, o, d, grad_rgb, grad_dist, ups, fcd, ffv, gtab, 9, nullptr, 0, gmlp, workspace,
+    rc = launch_backward_ws(ctx, n, o, d, grad_rgb, grad_dist, ups, fcd, ffv, gtab, 9, nullptr, gmlp, workspace,
                             st, det);
   }
   if (rc == NGPRT_OK && n_rec > 0) {

@@ -176,11 +176,10 @@ int launch_backward(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, c
 // at most 64 rays plus kSumGroups group sums, every element written before it
 // is read
 size_t backward_workspace_bytes(int64_t n);
-// tstride, astride: floats from one row of gtab / gatlas to the next (9 and
-// the atlas channels, or padded rows in a workspace)
+// tstride: floats from one row of gtab to the next (9, or padded rows)
 int launch_backward_ws(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, const float* grad_rgb,
                        const float* grad_dist, const float* ups, const float* fcd, const float* ffv,
-                       float* gtab, int tstride, float* gatlas, int astride, float* gmlp, float* workspace,
+                       float* gtab, int tstride, float* gatlas, float* gmlp, float* workspace,
                        hipStream_t s, const DetRecords& det = DetRecords());
 // the same with deterministic table gradients (hash model; allocates the
 // records, synchronises the stream)
