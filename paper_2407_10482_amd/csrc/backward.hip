@@ -756,11 +756,21 @@ static bool is_baked_model(const ngprt_ctx* ctx) { return ctx->desc.feature_mode
 constexpr int kPadRow = 16;
 constexpr size_t kPadMaxBytes = size_t(1) << 30;
 
-// Whether `rows` rows pay for it: they cost 200 bytes a row to clear, read and
-// add, 44 ps, and save the less the fewer rows a batch sends.  Measured
-// on the step of 2^18 rays, 16 x 2^19 tables: 16.7 -> 15.4 ms.
-static bool pad_pays(int64_t n, int64_t rows_per_level, int64_t rows) {
-  return n >= rows_per_level / 16 && size_t(rows) * kPadRow * sizeof(float) <= kPadMaxBytes;
+// Whether n rays' scatter into tables of T rows a level pays for them: they cost
+// 200 bytes a row to clear, read and add, and save a part of each row sent.
+// Measured, ms of a backward padded / not, rays of 15 to 17 samples:
+//   rays =          T/16         T/8          T/4          T/2
+//   8 x 2^14, box   .196 / .186  .213 / .203  .208 / .221  .252 / .268
+//   16 x 2^17, box  .944 / .956  1.57 / 1.64  2.50 / 2.80  4.25 / 4.68
+//   16 x 2^19, box  3.14 / 3.16  4.70 / 4.80  5.16 / 5.34  11.3 / 11.9
+//   same, contr.    3.27 / 3.13  4.72 / 4.54  8.03 / 7.90  14.5 / 14.7
+//   16 x 2^20, box  5.05 / 5.03  5.63 / 5.39  12.5 / 12.8  21.2 / 22.5
+// so from T/5 on; rays of three samples break even at T/2 to T (16 x 2^19: T/16
+// .870 / .591, T/4 1.24 / .99, T 4.03 / 4.03).  The baked model's rows, of 8
+// channels and on few levels, break even at T/2 (2 x 2^14: T/4 .162 / .157, T/2
+// .208 / .209, T .319 / .322, 16 T 1.78 / 1.89).
+static bool pad_pays(int64_t n, int64_t T, int64_t levels, bool baked) {
+  return n >= (baked ? T / 2 : T / 5) && size_t(levels * T) * kPadRow * sizeof(float) <= kPadMaxBytes;
 }
 
 __global__ void clear_rows_kernel(float4* __restrict__ p, int64_t n) {
@@ -835,7 +845,7 @@ int launch_backward(ngprt_ctx* ctx, int64_t n, const float* o, const float* d, c
   }
   const int64_t trows = int64_t(ctx->desc.n_levels) * ctx->T;
   const size_t floats = size_t(trows) * kPadRow;
-  float* rows = pad_pays(n, ctx->T, trows) ? padded_rows(ctx, floats * sizeof(float), st) : nullptr;
+  float* rows = pad_pays(n, ctx->T, ctx->desc.n_levels, baked) ? padded_rows(ctx, floats * sizeof(float), st) : nullptr;
   if (rows) {
     const int64_t n4 = int64_t(floats / 4);
     hipLaunchKernelGGL(clear_rows_kernel, dim3(unsigned((n4 + 255) / 256)), dim3(256), 0, st,

@@ -50,8 +50,8 @@ def _close(a, b):
     return float((a.double() - b.double()).norm()) <= TOL * float(b.double().norm())
 
 
-# batches that pad the tables' rows (2^14 a level: from 1,024 rays on)
-@pytest.mark.parametrize("name,n", [("tiny", 1024), ("tiny", 16500), ("baked_tiny", 16500)])
+# batches that pad the tables' rows (2^14 a level: from 3,276 rays on, baked from 8,192)
+@pytest.mark.parametrize("name,n", [("tiny", 3276), ("tiny", 16500), ("baked_tiny", 8192), ("baked_tiny", 16500)])
 def test_no_memory_for_padded_rows(name, n):
     """With the workspace at hand and no memory for the padded rows the call
     scatters into the caller's rows; a later call may pad again."""
@@ -78,9 +78,23 @@ def test_no_memory_for_padded_rows(name, n):
     assert all(_close(a, b) for a, b in zip(got, want))
 
 
+@pytest.mark.parametrize("name,n", [("tiny", 3275), ("tiny", 3276), ("baked_tiny", 8191), ("baked_tiny", 8192)])
+def test_around_the_rule(name, n):
+    """Either side of the line from which rows are padded, against the batch in
+    parts below it."""
+    print(f"[padded rows around the rule {name} {n}]", flush=True)
+    o, d, g = _rays(name, n)
+    r = gpu_renderer(name)
+    whole = _grads(r, o, d, g)
+    parts = [_grads(r, *(x[lo:hi].contiguous() for x in (o, d, g))) for lo, hi in ((0, 40), (40, 3000), (3000, n))]
+    for k, a in enumerate(whole):
+        b = parts[0][k] + parts[1][k] + parts[2][k]
+        assert float(b.abs().max()) > 0 and _close(a, b)
+
+
 def test_padded_rows_hold_at_most_one_gib():
-    """A baked scene whose tables (4 x 2^22) and atlas (2^15 blocks) would each
-    take 1 GiB of padded rows."""
+    """A baked scene whose tables (4 x 2^22) take 1 GiB of padded rows, and whose
+    atlas (2^15 blocks) would take as much."""
     import torch
     from paper_2407_10482_amd.renderer import Renderer
     print("[padded rows: memory held]", flush=True)
@@ -91,7 +105,7 @@ def test_padded_rows_hold_at_most_one_gib():
     r.load_mlp(torch.zeros((451,), device="cuda"))
     index = torch.arange(blocks, dtype=torch.int32, device="cuda").view(32, 32, 32)
     r.load_coarse(index, torch.zeros((blocks, 8, 8, 8, 16), device="cuda"), [0.0] * 16)
-    n = 1 << 20
+    n = 1 << 21                                           # T / 2: the tables' rows are padded
     o, g = torch.zeros((n, 3), device="cuda"), torch.ones((n, 3), device="cuda")
     d = torch.zeros((n, 3), device="cuda")                # rays without a direction: no samples
     grads = [torch.zeros(s, device="cuda") for s in ((4, 1 << 22, 9), (blocks, 8, 8, 8, 16), (451,))]
@@ -101,7 +115,7 @@ def test_padded_rows_hold_at_most_one_gib():
     r.backward_baked(o, d, g, *grads)
     torch.cuda.synchronize()
     held = before - torch.cuda.mem_get_info()[0]
-    # the rows, 30 MB of partials, and the allocator's rounding
+    # the rows, 59 MB of partials, and the allocator's rounding
     assert (1 << 30) <= held <= (1 << 30) + (128 << 20), held
     assert float(grads[0].abs().max()) == 0.0 and float(grads[1].abs().max()) == 0.0
 
