@@ -1,6 +1,6 @@
 """Renders on either side of the lanes-a-ray rule's lines (16, 8 or one lane a
-ray by launch size and domain; one for rays of at most three samples): the
-same bits whatever the launch a ray is part of."""
+ray by launch size and domain, one beyond 16,384 rays of at most three samples):
+the same bits whatever the launch a ray is part of."""
 import dataclasses
 
 import numpy as np
@@ -41,7 +41,7 @@ def test_same_bits_across_the_lines(domain, dtype, max_samples):
     for labels in (False, True):
         want = render(81921, labels)
         assert int(want["n_samples"].max()) >= min(max_samples, 17)
-        for n in (17, line - 1, line, line + 1, line + 7, 81913, 81920):
+        for n in (17, 16384, 16385, line - 1, line, line + 1, line + 7, 81913, 81920):
             got = render(n, labels)
             for k, v in got.items():
                 assert torch.equal(v.view(torch.int32), want[k][:n].contiguous().view(torch.int32)), (n, labels, k)
