@@ -435,7 +435,7 @@ int ngprt_render_backward_baked(ngprt_ctx* ctx, int64_t n_rays, const float* dev
  * directions, C_d [n][3] and F [n][4] as ngprt_render wrote them, dL/drgb
  * [n][3].  Writes dL/dC_d and dL/dF to dev_grad_cf, float32 [n][7]
  * (C_d first), and accumulates (+=) dL/dpsi into dev_grad_mlp [5891] (the
- * caller zeroes it; partial sums per 64 rays added in a fixed order).  SH(d)
+ * caller zeroes it; the workgroups' partial sums added in a fixed order).  SH(d)
  * is a constant input.  May grow the library workspace. */
 int ngprt_view_mlp_backward(ngprt_ctx* ctx, int64_t n_rays, const float* dev_dirs, const float* dev_c_d,
                             const float* dev_feat, const float* dev_grad_rgb, float* dev_grad_cf,

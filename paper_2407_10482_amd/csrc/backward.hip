@@ -7,10 +7,10 @@
 //          (the same float32 values; not with the regulariser, whose sums
 //          this pass also forms); then, per
 //          lane, the deferred MLP forward and backward give dL/dC_d, dL/dF,
-//          and per-ray outer products whose sum over the wave's 64 rays is
-//          taken on v_mfma_f32_16x16x4_f32 (K = rays) and written as one
-//          451-float partial per wave (with the view-dependent MLP, dL/dC_d
-//          and dL/dF come per ray from its own backward instead, `ups`);
+//          and per-ray outer products whose sum over the workgroup's 16 or 64
+//          rays is taken on v_mfma_f32_16x16x4_f32 (K = rays) and written as
+//          one 451-float partial per workgroup (with the view-dependent MLP,
+//          dL/dC_d and dL/dF come per ray from its own backward, `ups`);
 //  pass 2  re-march again with the same decisions; at each sample
 //          dL/dsigma_i = delta (T_{i+1} s_i - (S - P_i)) with
 //          s_i = dL/dC_d . c_i + dL/dF . v_i, S = dL/dC_d . C_d + dL/dF . F and
@@ -25,7 +25,7 @@
 //          The baked model scatters into its fine levels and coarse atlas
 //          rows instead (baked_scatter).  In the deterministic mode each
 //          contribution goes to a record of its own instead (det.hip).
-// The per-wave MLP partials are then added in a fixed order (reduce.h).
+// The workgroups' MLP partials are then added in a fixed order (reduce.h).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -727,6 +727,10 @@ __global__ void adam_kernel(int64_t n, float* __restrict__ p, const float* __res
 // 3.83 / 5.41 ms, 2^15 rays 2.14 / 1.25 / 0.97 / 0.95 / 1.25, 2^14 rays 1.93 /
 // 1.27 / 0.90 / 0.82 / 0.86 (0.89 at 4 and 0.76 at 16 with the fill rule of
 // march_slots), 2^10 rays 2.29 / 1.24 / 0.83 / 0.67 / 0.64 ms.
+// Lanes past a ray's last sample look up for nothing, so rays of about one
+// sample lose by it (16 x 2^19 tables, 16,384 rays of 1.2 samples .38 ms with one
+// lane a ray, .48 so; 2^18 rays 1.20 against 1.82, .25 of it padded rows); from
+// 2.5 samples on they gain.
 static int backward_slots(int64_t n) { return n <= 16384 ? 16 : 4; }
 
 // workgroups of m rays of a batch of n

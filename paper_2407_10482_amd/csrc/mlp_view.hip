@@ -220,7 +220,7 @@ __global__ void __launch_bounds__(64 * kViewWaves) view_mlp_kernel(int64_t n, co
 // their operands hold a unit a lane where the products above leave a ray a
 // lane, so each is transposed through 5 KB of LDS a wave (rows of 20 floats:
 // both the stores and the 16-byte loads spread over all banks; slot s takes rays
-// 4 s .. 4 s + 3, in both operands).  The sums stay in 118 accumulators a lane over
+// 4 s .. 4 s + 3, in both operands).  The sums stay in 117 accumulators a lane over
 // all rays of a wave, then a workgroup's eight waves are added in a fixed order
 // and written as one 5891-float partial; the partials are added in a fixed
 // order too (reduce.h).  A constant input of 1 (weight 0) gives db0.

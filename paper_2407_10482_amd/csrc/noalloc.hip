@@ -2,8 +2,8 @@
 // that cannot allocate device memory (code under stream capture, tight
 // training loops, hosts that forbid allocation).
 //
-// Its workspace (one MLP-gradient partial per wave of 64 rays plus the
-// fixed-order group sums, see reduce.h) lives in a file-scope device array
+// Its workspace (one MLP-gradient partial per workgroup of 64 or 16 rays plus
+// the fixed-order group sums, see reduce.h) lives in a file-scope device array
 // of fixed size instead of the context's grow-on-demand buffer.  Every GPU
 // that loads the library holds its own copy of the array until the process
 // ends; its device address is looked up once per device, with that device
