@@ -804,7 +804,8 @@ static int launch_add_rows(ngprt_ctx* ctx, const float* src, float* dst, int64_t
 // The context's padded rows, grown to `bytes`; NULL when they cannot be had.
 // They are kept apart from the workspace: a backward needs the workspace, the
 // padded rows only make its scatter faster, so a device too full for them still
-// trains (on the caller's rows).
+// trains (on the caller's rows).  Nor are they taken while the stream is being
+// captured: that memory would be the graph's, and the context keeps it.
 // The rows begin kPadShift into their buffer: large buffers, the tables' too,
 // start on 2 MiB boundaries, and rows aligned alike cost the steps more (a
 // step's time with the rows at 0 / 6,464 / 2^20 / 2^20 + 6,464 bytes: 8 x 2^14
@@ -813,6 +814,11 @@ constexpr size_t kPadShift = (size_t(1) << 20) + 101 * 64;
 static float* padded_rows(ngprt_ctx* ctx, size_t bytes, hipStream_t st) {
   bytes += kPadShift;
   if (bytes > ctx->pad_bytes) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
     if (ctx->pad_rows) (void)hipFreeAsync(ctx->pad_rows, st);
     ctx->pad_rows = nullptr;
     ctx->pad_bytes = 0;

@@ -160,3 +160,31 @@ def test_more_threads_than_a_launch_holds():
     got = _grads(gpu_renderer("tiny"), *big)
     torch.cuda.synchronize()
     assert all(float(b.abs().max()) > 0 and _close(a, b) for a, b in zip(got, want))
+
+
+def test_capture_before_the_rows_are_there():
+    """A captured backward whose workspace is at hand takes no memory for padded
+    rows; replays with eager work between them, padded eager calls included."""
+    import torch
+    print("[padded rows: capture]", flush=True)
+    n = 4096
+    o, d, g = _rays("tiny", n)
+    want = _grads(gpu_renderer("tiny"), o, d, g)
+    r = gpu_renderer("tiny")
+    r.set_deterministic(True)                             # takes the workspace, no rows
+    _grads(r, o, d, g)
+    r.set_deterministic(False)
+    gt, gm = torch.zeros_like(want[0]), torch.zeros_like(want[1])
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        r.backward(o, d, g, gt, gm)
+    for k in range(4):
+        gt.zero_()
+        gm.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert _close(gt, want[0]) and _close(gm, want[1])
+        if k:
+            eager = _grads(r, o, d, g)                    # padded: the rows are taken now
+            assert _close(eager[0], want[0])
